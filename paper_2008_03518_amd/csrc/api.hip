@@ -69,6 +69,12 @@ struct fastmdp_ctx {
     std::vector<int> hRowN;
     int n_plans = 0;
     int seq = 0;                          // next request sequence number (table entry owners are below it)
+    // the rows' grids (fmdp::DevTable): built, over at most gridRowN entries
+    // of each row (empty: built during a planning call, whose row counts the
+    // host does not hold) when the table held grid_plans plans
+    bool grid_ok = false;
+    std::vector<int> gridRowN;
+    int grid_plans = 0;
     std::vector<int> snapRowN;            // table snapshot (row counts)
     int snap_plans = 0;
     float *dTerr = nullptr;
@@ -148,6 +154,7 @@ int dev_alloc(T **p, size_t n) {
 void free_all(fastmdp_ctx *c) {
     hipFree(c->tb.X); hipFree(c->tb.Y); hipFree(c->tb.Z); hipFree(c->tb.rowN);
     hipFree(c->tb.vis); hipFree(c->tb.own); hipFree(c->tb.dead);
+    hipFree(c->tb.Q); hipFree(c->tb.grec); hipFree(c->tb.goff); hipFree(c->tb.gn);
     hipFree(c->dDlRow); hipFree(c->dDlCol); hipFree(c->dDlEp); hipFree(c->dDlLen); hipFree(c->dDlStart);
     hipFree(c->dDlOwn); hipFree(c->dDlX); hipFree(c->dDlY);
     hipFree(c->dRowNPre); hipFree(c->dInsList); hipFree(c->dInsN); hipFree(c->dBox);
@@ -249,6 +256,38 @@ void make_devcfg(const fastmdp_config &c, DevCfg &d) {
     double max_abs = 0.0;
     for (int k = 0; k < 3; ++k) max_abs = std::max({max_abs, std::fabs(c.box_min[k]), std::fabs(c.box_max[k])});
     d.cull_box = (float)(std::sqrt((double)d.cull_r2) * 1.001 + 1.0 + max_abs * 1e-6);
+    // Two goal terms differ by more than the tie band when their distances
+    // differ by more than m ell / |log gamma|, m = -log(1 - tie_rel) plus
+    // what the rounding of the two computed terms can hide: below 1e-12
+    // while the exponent |log gamma| d / ell is at most 600 (the exponent's
+    // relative error is a few 2^-53, the exponential's as well).
+    d.run_ok = d.abs_r_goal > 0.0 && c.tie_rel <= 1e-3 ? 1 : 0;
+    d.run_c1 = c.n_head > 1 ? std::cos(2.0 * M_PI / c.n_head) : -1e9;
+    // half-widths of the box test on 16-bit coordinates: the staging radius
+    // plus both roundings (half a step each), the FP32 arithmetic's and the
+    // FP32 state's (under a step together)
+    d.run_r = d.run_w = d.run_step = 0u;
+    for (int k = 0; k < 2; ++k) {
+        const double scale = 65535.0 / (c.box_max[k] - c.box_min[k]);
+        const double r = std::ceil(std::sqrt((double)d.cull_r2) * 1.001 * scale) + 3.0;
+        const double m = std::ceil(d.max_step * scale);
+        const bool fits = r > 0.0 && m >= 0.0 && r + 32.0 * m < 32000.0;
+        if (!fits) d.run_ok = 0;
+        d.run_r |= (fits ? (uint32_t)r : 0u) << (16 * k);
+        d.run_w |= (fits ? 2u * (uint32_t)r : 0xffffu) << (16 * k);
+        d.run_step |= (fits ? (uint32_t)m : 0u) << (16 * k);
+    }
+    // The goal terms of a step's actions differ by at most the factor
+    // gamma^-(2 max_step / ell); an action inside a well loses at least the
+    // well's value at its radius.
+    const double well = d.abs_r_intr * std::exp(d.log_gamma_intr * (c.R_intr / d.ell)) * (1.0 - 1e-9);
+    const double spread = std::exp(-d.log_gamma * (2.0 * d.max_step / d.ell)) - 1.0;
+    d.detour_ok = d.run_ok && d.abs_r_goal * (spread * (1.0 + 1e-9) + 2.0 * c.tie_rel + 1e-9) < well ? 1 : 0;
+    d.run_margin = (-std::log1p(-std::min(c.tie_rel, 0.5)) * 1.001 + 2e-12) * d.ell / std::fabs(d.log_gamma);
+    d.run_dmax = 600.0 * d.ell / std::fabs(d.log_gamma);
+    d.run_v = 0;
+    for (int v = 1; v < c.n_speed; ++v)
+        if (c.speed[v] > c.speed[d.run_v]) d.run_v = v;
     d.planner_threads = c.planner_threads;
     d.n_cu = 256;                          // the device's count is set once the context knows it
 }
@@ -279,6 +318,21 @@ int timed_planner(fastmdp_ctx *c, int nblk, const int *list, int budget, int val
     if (!sync) return 0;                     // the caller synchronises, then calls planner_time
     HIP_TRY(hipEventSynchronize(c->e1));
     return planner_time(c);
+}
+
+// The rows' grids, before a range-query planner launch: built when there are
+// none, or when the entries appended since (searched one by one) have grown
+// to a quarter of the indexed ones.  `limit` as launch_build_grid; in_call:
+// during a planning call.
+int refresh_grid(fastmdp_ctx *c, int limit, bool in_call) {
+    if (!fmdp::uses_range_planner(c->dc, c->prop.mode)) return 0;
+    if (c->grid_ok && c->n_plans - c->grid_plans < std::max(in_call ? 1024 : 256, c->grid_plans / 4)) return 0;
+    HIP_TRY(fmdp::launch_build_grid(c->tb, limit, c->stream));
+    c->grid_ok = true;
+    c->grid_plans = c->n_plans;
+    if (in_call) c->gridRowN.clear();
+    else c->gridRowN = c->hRowN;
+    return 0;
 }
 
 void reset_stats(fastmdp_ctx *c) {
@@ -409,6 +463,12 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     c->stride = cfg->max_steps + 1;
     c->tb.cap = cfg->plan_capacity;
     c->tb.rows = cfg->max_rows;
+    c->tb.qx0 = (float)cfg->box_min[0];
+    c->tb.qy0 = (float)cfg->box_min[1];
+    c->tb.qsx = (float)(65535.0 / (cfg->box_max[0] - cfg->box_min[0]));
+    c->tb.qsy = (float)(65535.0 / (cfg->box_max[1] - cfg->box_min[1]));
+    c->tb.gsx = (float)(fmdp::kGrid / (cfg->box_max[0] - cfg->box_min[0]));
+    c->tb.gsy = (float)(fmdp::kGrid / (cfg->box_max[1] - cfg->box_min[1]));
     const size_t tsz = (size_t)cfg->max_rows * cfg->plan_capacity;
     const size_t ssz = (size_t)c->max_slots * c->stride;
     rc = 0;
@@ -418,6 +478,12 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     rc = rc ? rc : dev_alloc(&c->tb.vis, tsz);
     rc = rc ? rc : dev_alloc(&c->tb.own, tsz);
     rc = rc ? rc : dev_alloc(&c->tb.dead, tsz);
+    if (fmdp::uses_range_planner(c->dc, FASTMDP_PROPOSE_NONE)) {
+        rc = rc ? rc : dev_alloc(&c->tb.Q, tsz);
+        rc = rc ? rc : dev_alloc(&c->tb.grec, tsz);
+        rc = rc ? rc : dev_alloc(&c->tb.goff, (size_t)cfg->max_rows * (fmdp::kGridCells + 1));
+        rc = rc ? rc : dev_alloc(&c->tb.gn, (size_t)cfg->max_rows);
+    }
     rc = rc ? rc : dev_alloc(&c->tb.rowN, (size_t)cfg->max_rows);
     rc = rc ? rc : dev_alloc(&c->dSlots, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->dList, (size_t)c->max_slots);
@@ -506,6 +572,7 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     c->hRowN.assign(cfg->max_rows, 0);
     c->hRowTmp.assign(cfg->max_rows, 0);
     if (fmdp::launch_fill_int(c->tb.rowN, 0, cfg->max_rows, c->stream) != hipSuccess ||
+        (c->tb.gn && fmdp::launch_fill_int(c->tb.gn, 0, cfg->max_rows, c->stream) != hipSuccess) ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
         free_all(c);
         delete c;
@@ -669,9 +736,11 @@ int fastmdp_plan_request(fastmdp_ctx *ctx, const fastmdp_request *req, fastmdp_p
     std::lock_guard<std::mutex> lk(ctx->mu);
     reset_stats(ctx);
     Slot s = fresh_slot(*req, 0, ctx->seq);
+    int rc = refresh_grid(ctx, ctx->seq, false);
+    if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(ctx->dSlots, &s, sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
-    int rc = timed_planner(ctx, 1, nullptr, ctx->cfg.max_steps + 1, 0, 0, none);
+    rc = timed_planner(ctx, 1, nullptr, ctx->cfg.max_steps + 1, 0, 0, none);
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(&s, ctx->dSlots, sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -703,9 +772,11 @@ int fastmdp_plan_departures(fastmdp_ctx *ctx, const fastmdp_request *req, int32_
         r.t0 = t0[i];
         hs[i] = fresh_slot(r, i, ctx->seq);            // every candidate sees the same table
     }
+    int rc = refresh_grid(ctx, ctx->seq, false);
+    if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(ctx->dSlots, hs, n * sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
-    int rc = timed_planner(ctx, n, nullptr, ctx->cfg.max_steps + 1, 1, 0, none);
+    rc = timed_planner(ctx, n, nullptr, ctx->cfg.max_steps + 1, 1, 0, none);
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(hs, ctx->dSlots, n * sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -851,7 +922,12 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
         return rc;
     };
     auto run = [&]() -> int {
+        int rc0 = refresh_grid(ctx, seq0, false);
+        if (rc0) return rc0;
         while (next_commit < n) {
+            // a call that grows the table far: its accepted plans indexed too
+            if (next_commit > 0) rc0 = refresh_grid(ctx, seq0 + next_commit, true);
+            if (rc0) return rc0;
             // admit arrived requests into free slots, in request order
             bool dirty = false;
             const double t_now = arrival_s ? now_s() : 0.0;
@@ -1026,6 +1102,10 @@ int fastmdp_table_rewind(fastmdp_ctx *ctx) {
     HIP_TRY(hipMemcpyAsync(ctx->tb.rowN, ctx->snapRowN.data(), ctx->snapRowN.size() * sizeof(int),
                            hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    // the grids stand while they index no entry that is dropped here
+    bool covered = ctx->gridRowN.size() == ctx->snapRowN.size();
+    for (size_t r = 0; covered && r < ctx->snapRowN.size(); ++r) covered = ctx->gridRowN[r] <= ctx->snapRowN[r];
+    ctx->grid_ok = ctx->grid_ok && covered;
     ctx->hRowN = ctx->snapRowN;
     ctx->n_plans = ctx->snap_plans;
     return 0;
@@ -1207,6 +1287,11 @@ int fastmdp_load_table(fastmdp_ctx *ctx, const char *path) {
     std::fclose(f);
     if (hipMemcpy(ctx->tb.rowN, rowN.data(), rows * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
         return FASTMDP_E_DEVICE;
+    if (ctx->tb.Q) {
+        HIP_TRY(fmdp::launch_quantise_table(ctx->tb, ctx->stream));
+        HIP_TRY(hipStreamSynchronize(ctx->stream));
+    }
+    ctx->grid_ok = false;
     ctx->hRowN.swap(rowN);
     ctx->n_plans = hdr[2];
     return 0;

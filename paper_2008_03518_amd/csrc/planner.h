@@ -55,6 +55,18 @@ struct DevCfg {
     float cull_box;                      // half-width of the range-query box test on x and y: the
                                          // staging radius plus a margin for every rounding of the
                                          // exact test (FP32 offsets of coordinates up to max_abs)
+    // runs of steps that no plan affects (range.hip): the goal-directed
+    // action is the choice when every other action's successor is farther
+    // from the goal by more than run_margin, while the goal is within
+    // run_dmax; run_v is the fastest speed, run_c1 the largest cosine of the
+    // other headings' offsets, run_ok 0 where the goal term does not decide
+    // (no goal reward, a wide tie band) or the box test's half-widths run_r
+    // (in steps of the table's 16-bit x | y << 16) do not fit
+    double run_margin, run_dmax, run_c1;
+    uint32_t run_r, run_w, run_step;     // run_w: the box's widths (everything where they do not fit);
+                                         // run_step: the longest action step in the same units
+    int run_v, run_ok;
+    int detour_ok;                       // an action inside a well never beats one outside every well
     int planner_threads;                 // full-sweep path: 0 (automatic), kRangeThreads, kRangeThreadsSolo,
                                          // kPlanThreads
     int n_cu;                            // compute units of the device
@@ -70,6 +82,16 @@ struct DevCfg {
 struct DevTable {
     float *X, *Y, *Z;
     int *vis, *own, *dead;
+    // Range-query planner (null without): 16-bit box coordinates of every
+    // entry (x | y << 16, quantised below), and per row the entries before
+    // column gn[t] that stand, by cell of a kGrid x kGrid grid over the box:
+    // records (x, y, z, visibility bits) of cell c of row t at grec[t * cap +
+    // goff[t * (kGrid^2 + 1) + c] ..).  Later columns are searched one by one.
+    uint32_t *Q;
+    float4 *grec;
+    int *goff, *gn;
+    float qx0, qy0, qsx, qsy;            // box corner, 16-bit steps per metre
+    float gsx, gsy;                      // cells per metre
     int *rowN;
     int cap, rows;
     const float *terr;                   // nullptr without terrain
@@ -170,6 +192,24 @@ struct PropArgs {
     PropNet net;
 };
 
+constexpr int kGrid = 32;            // cells per side (a query's box covers about two per side of a 30 km box)
+constexpr int kGridCells = kGrid * kGrid;
+constexpr int kGridMin = 256;        // rows of fewer entries are searched one by one
+
+// Grid cell of a coordinate (clamped to the box; never decreases with it).
+__device__ __forceinline__ int grid_cell(float x, float x0, float gs) {
+    return (int)fminf(fmaxf((x - x0) * gs, 0.0f), (float)(kGrid - 1));
+}
+
+// 16-bit box coordinates of an entry, x | y << 16, clamped to the box: a
+// quarter of the bytes of its x and y and one subtraction for both, for a
+// box test that leaves a superset of the entries near a state.
+__device__ __forceinline__ uint32_t quantised(const DevTable &tb, float x, float y) {
+    const float a = fminf(fmaxf((x - tb.qx0) * tb.qsx + 0.5f, 0.0f), 65535.0f);
+    const float b = fminf(fmaxf((y - tb.qy0) * tb.qsy + 0.5f, 0.0f), 65535.0f);
+    return (uint32_t)a | (uint32_t)b << 16;
+}
+
 // Entry j of a row (absolute index idx) is visible to the request with
 // sequence number seq.
 __device__ __forceinline__ bool entry_visible(const DevTable &tb, size_t idx, int seq) {
@@ -266,6 +306,11 @@ int mlp_weights(const fastmdp_mlp *m, PropNet *w);
 
 // table.hip
 hipError_t launch_fill_int(int *p, int value, int n, hipStream_t st);
+// The 16-bit coordinates of every entry in use (after a table was loaded whole).
+hipError_t launch_quantise_table(const DevTable &t, hipStream_t st);
+// Every row's grid over its longest prefix of entries that stay as they are:
+// owned by sequence numbers below `limit` (accepted) or withdrawn.
+hipError_t launch_build_grid(const DevTable &t, int limit, hipStream_t st);
 hipError_t launch_scatter_points(const DevTable &t, const float *pts, const int *rows, const int *cols, int n,
                                  int own, hipStream_t st);
 // Append n plans (t0[j], len[j], points plan-major in xyz; all device

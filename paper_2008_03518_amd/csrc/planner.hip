@@ -431,7 +431,7 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
         const double s[3] = {st_s[0], st_s[1], st_s[2]};
         if (!eval) {
             const double ex = g[0] - s[0], ey = g[1] - s[1], ez = g[2] - s[2];
-            if (sqrt(ex * ex + ey * ey + ez * ez) <= cfg.ell) {
+            if (sqrt(norm2(ex, ey, ez)) <= cfg.ell) {
                 lds_barrier();
                 if (tid == 0) st_status = FASTMDP_OK;
                 break;
@@ -446,11 +446,11 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
 
         // 1. heading directions: the goal bearing rotated by each offset
         const double bx = g[0] - s[0], by = g[1] - s[1];
-        const double br = sqrt(bx * bx + by * by);
+        const double br = sqrt(dot2(bx, bx, by, by));
         const double cb = br > 0.0 ? bx / br : 1.0, sb = br > 0.0 ? by / br : 0.0;
         for (int h = tid; h < H; h += NT) {
-            sCos[h] = cb * sC0[h] - sb * sS0[h];
-            sSin[h] = sb * sC0[h] + cb * sS0[h];
+            sCos[h] = dot2(cb, sC0[h], -sb, sS0[h]);
+            sSin[h] = dot2(sb, sC0[h], cb, sS0[h]);
         }
         const int row = t + 1;
         const int n_row = pre_n;

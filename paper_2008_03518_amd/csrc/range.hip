@@ -43,7 +43,6 @@ namespace fmdp {
 
 namespace {
 
-constexpr int RAW = 4096;                    // row entries per chunk (x and y in LDS)
 constexpr int HMAX = kRangeMaxHeads;
 
 __device__ __forceinline__ int lanes_below(uint64_t bal) {
@@ -60,19 +59,24 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     DevCfg cfg, DevTable tb, Slot *slots, const int *slot_list, Traj tr, int budget, int validate, int epoch,
     LaunchStop stop) {
     constexpr int NW = NT / 64;
-    constexpr int G4 = RAW / (4 * NT);           // four-entry groups per lane and chunk
     constexpr int TILE = NT;                     // staged entries per round: one candidate per thread
     constexpr int APT = kMaxActions / NT;        // actions per thread
-    static_assert(RAW % (4 * NT) == 0, "a chunk is a whole number of four-entry groups per lane");
-    static_assert(4 * G4 <= 32, "a lane's candidates of a chunk fit one 32-bit mask");
+    constexpr int RUN = 16;                      // steps of a run: four lanes of the checking wave each
+    constexpr int DS = 8;                        // steps of a detour batch
+    constexpr int DL = 32;                       // entries listed per detour step
+    constexpr int RING = 128;                    // points on their way to the trajectory
+    static_assert(64 + 4 * RUN <= RING, "points are written before the ring wraps");
+    static_assert(NW >= 3 && DS % NW == 0 && DS <= RUN, "a run's roles and a detour batch's rows are dealt to the waves");
     static_assert(kMaxActions % NT == 0, "actions are dealt to threads in whole rounds");
     static_assert(HMAX <= NT, "one thread per heading");
-    // the row chunk's x, y by DMA; alone on its CU (LDS to spare) also z
-    // and visibility, so that a candidate's exact test reads no memory
-    constexpr bool ZV = NT == kRangeThreadsSolo;
-    __shared__ __attribute__((aligned(16))) float rawX[RAW], rawY[RAW];
-    __shared__ __attribute__((aligned(16))) float rawZ[ZV ? RAW : 4];
-    __shared__ __attribute__((aligned(16))) int rawV[ZV ? RAW : 4];
+    __shared__ float4 sList[DS][DL];            // detour batch: each row's entries near the batch's states
+    __shared__ int sListN[DS];
+    // detour step, per wave (alternate steps): its nearest action outside
+    // the wells: distance to the goal, successor, nearest plan, action, how
+    // many of its lanes come as near
+    __shared__ double sR[2][NW][5];
+    __shared__ int sRa[2][NW], sRn[2][NW];
+    __shared__ double sC0[HMAX], sS0[HMAX];              // heading offsets (cos, sin of 2*pi*h/H)
     __shared__ float4 tile[TILE];               // staged entries of one round; validation point list
     __shared__ double sCos[2][HMAX], sSin[2][HMAX];      // heading directions, alternate steps
     __shared__ double sStep[FASTMDP_MAX_ACT_DIM], sDz[FASTMDP_MAX_ACT_DIM];   // speed*dt, climb*dt
@@ -82,7 +86,20 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     __shared__ int s_wsum[NW], s_rem[2][NW];
     __shared__ int s_wli[NW], s_wti[NW], s_wfl[NW];      // per wave: choice, largest, choice's flags
     __shared__ double s_wv[NW], s_wd2[NW];               // per wave: choice's value, nearest distance
-    __shared__ int s_any, s_flag, s_stop;
+    __shared__ int s_any, s_flag, s_stop, s_stop_run[2];
+    // the points taken last, written to the trajectory 64 at a time: point i
+    // in slot i % RING; value (runs leave it to the write), nearest squared
+    // distance, action | run << 16, row entries seen, top action
+    __shared__ double sP[RING][3], sPv[RING], sPd[RING];
+    __shared__ int sPa[RING], sPs[RING], sPt[RING];
+    // runs (alternate batches): steps and action, directions and distances;
+    // per step the findings among the indexed and the later columns: nearest
+    // (sweep expression), entries in reach, and whether the rest holds
+    __shared__ double sQ[2][RUN][3];
+    __shared__ int sNb[2], sAg[2];
+    __shared__ float sMg[2][RUN], sMt[2][RUN];
+    __shared__ int sNg[2][RUN], sNt[2][RUN], sOk[2][RUN];
+    __shared__ int sCnt[128], sGn[128];                  // entry counts and indexed columns of rows wb .. wb + 127, by row % 128
     const ActTab at{sStep, sDz};
 
     const int tid = threadIdx.x;
@@ -98,11 +115,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     const size_t pt_base = (size_t)slot * tr.stride;
 
     // this thread's heading offset 2*pi*h/H (h = tid < H)
-    double c0 = 0.0, s0 = 0.0;
     if (tid < H) {
         const double th = 2.0 * M_PI * (double)tid / (double)H;
-        c0 = cos(th);
-        s0 = sin(th);
+        sC0[tid] = cos(th);
+        sS0[tid] = sin(th);
     }
     if (tid < FASTMDP_MAX_ACT_DIM) {
         sStep[tid] = cfg.speed[tid] * cfg.dt;
@@ -158,68 +174,126 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         if (blocked) status = FASTMDP_REJECT_ORIGIN;
     }
 
-    auto row_count = [&](int row) { return (row >= 0 && row < tb.rows) ? min(tb.rowN[row], tb.cap) : 0; };
-    // Entries [base, base + min(cnt - base, RAW)) of a row: x and y (and z
-    // and visibility with ZV) travel
-    // from the table to LDS without registers (global_load_lds), 16 bytes
-    // (four entries) per lane and instruction; entry base + j lands at
-    // raw*[j], in the slots of the lane that later tests it, so a wave waits
-    // only for its own loads and a lane may refill its slots once it has
-    // read them.  A group that runs past the row's count stays inside the
-    // row's capacity (a multiple of four), so every read is in bounds.
-    auto load_xy = [&](int row, int base, int cnt) {
-        const size_t rb = (size_t)row * tb.cap + base;
-        const int lim = min(cnt - base, RAW);
-        int ofs = 4 * tid;
-        asm volatile("" : "+v"(ofs));
+    // Entry counts and indexed columns of 128 rows from wb on (the table does
+    // not change during a launch), 64 rows at a time by one wave, a full 64
+    // rows before they are read
+    int wb = t0 + n;
+    auto read_counts = [&](int first) {
+        const int r = first + lane;
+        const bool in = r >= 0 && r < tb.rows;
+        sCnt[r & 127] = in ? min(tb.rowN[r], tb.cap) : 0;
+        sGn[r & 127] = in ? tb.gn[r] : 0;
+    };
+    if (wave < 2) read_counts(wb + 64 * wave);
+    auto row_count = [&](int row) { return sCnt[row & 127]; };
+    auto row_indexed = [&](int row) { return sGn[row & 127]; };
+    auto shift_counts = [&](int row) {                    // uniform: the rows before `row` are not read again
+        if (row - wb >= 64) {
+            if (wave == NW - 1) read_counts(wb + 128);
+            wb += 64;
+        }
+    };
+    // The exact test of the range query for one entry (x, y, z, visibility)
+    // against a state: e its staged form.
+    auto near_entry = [&](const float4 r, double x, double y, double z, float4 &e) {
+        const float qx = (float)((double)r.x - x);
+        const float qy = (float)((double)r.y - y);
+        const float qz = (float)((double)r.z - z);
+        const float w = fmaf(qx, qx, fmaf(qy, qy, qz * qz));
+        e = make_float4(qx, qy, cfg.zeta_scale * qz, w);
+        return __float_as_int(r.w) < seq && w < cfg.cull_r2;
+    };
+    auto table_entry = [&](size_t idx) {
+        return make_float4(tb.X[idx], tb.Y[idx], tb.Z[idx], __int_as_float(tb.vis[idx]));
+    };
+    // 16-bit box test: both offsets from the box's corner at most its width
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 q_half = __builtin_bit_cast(u16x2, cfg.run_r), q_width = __builtin_bit_cast(u16x2, cfg.run_w);
+    auto q_corner = [&](double x, double y, u16x2 half) {
+        return (u16x2)(__builtin_bit_cast(u16x2, quantised(tb, (float)x, (float)y)) - half);
+    };
+    // bits of the entries j .. j + 3 (columns [from, n_row) only) inside the box
+    auto q_inside = [&](const uint4 q, u16x2 corner, u16x2 q_width, int j, int from, int n_row) -> uint32_t {
+        const uint32_t e4[4] = {q.x, q.y, q.z, q.w};
+        uint32_t o[4], bits = 0u;
 #pragma unroll
-        for (int i = 0; i < G4; ++i) {
-            const int j0 = i * 4 * NT + wave * 256;        // wave-uniform LDS destination
-            const int j = ofs + i * 4 * NT;
-            if (j < lim) {
-                load_lds16(tb.X + rb + j, rawX + j0);
-                load_lds16(tb.Y + rb + j, rawY + j0);
-                if constexpr (ZV) {
-                    load_lds16(tb.Z + rb + j, rawZ + j0);
-                    load_lds16(tb.vis + rb + j, rawV + j0);
-                }
-            }
+        for (int i = 0; i < 4; ++i)
+            o[i] = __builtin_bit_cast(
+                uint32_t, __builtin_elementwise_sub_sat((u16x2)(__builtin_bit_cast(u16x2, e4[i]) - corner), q_width));
+        if (__ballot(min(min(o[0], o[1]), min(o[2], o[3])) == 0u)) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (o[i] == 0u && j + i >= from && j + i < n_row) bits |= 1u << i;
+        }
+        return bits;
+    };
+    // cells a query around (x, y) covers (one metre more than the box test)
+    const float g_half = cfg.cull_box + 1.0f;
+    struct Cells {
+        int x0, x1, y0, y1;
+    };
+    auto cells = [&](float x, float y, float g_half) {
+        Cells c;
+        c.x0 = __builtin_amdgcn_readfirstlane(grid_cell(x - g_half, tb.qx0, tb.gsx));
+        c.x1 = __builtin_amdgcn_readfirstlane(grid_cell(x + g_half, tb.qx0, tb.gsx));
+        c.y0 = __builtin_amdgcn_readfirstlane(grid_cell(y - g_half, tb.qy0, tb.gsy));
+        c.y1 = __builtin_amdgcn_readfirstlane(grid_cell(y + g_half, tb.qy0, tb.gsy));
+        return c;
+    };
+    // records [a, b) of this lane's row of cells: y on lanes below 32, y + 1
+    // above; this lane's first record in a, later ones 32 on
+    auto cell_range = [&](int row, const Cells &c, int y, int &a, int &b) {
+        const int yy = y + (lane >> 5);
+        a = b = 0;
+        if (yy <= c.y1) {
+            const int *off = tb.goff + (size_t)row * (kGridCells + 1) + yy * kGrid;
+            a = off[c.x0];
+            b = off[c.x1 + 1];
         }
     };
 
-    // rows in flight: pre_n entries of the next step's row (its x, y loading
-    // into LDS) and nn, the count of the row after it
-    int pre_n = 0, nn = 0;
-    {
-        const int row = t0 + n;
-        pre_n = row_count(row);
-        if (pre_n > 0) load_xy(row, 0, pre_n);
-        nn = row_count(row + 1);
-    }
-
-    long long pairs = 0, entries = 0;
-    int steps_here = 0, stop_v = 0, buf = 0;
-    const float cbox = cfg.cull_box;
-    // The point taken by a step is written to the trajectory during the
-    // next step's valuation, by the last wave, which scores no action in at
-    // least one round (with 360 actions or fewer) and so waits there: its
-    // coordinates are the state, its value and nearest distance stay in
-    // s_wv / s_wd2 of the winning wave until the next argmax, the rest in
-    // registers (the same in every thread).  pend: a point is not yet written.
-    int pend = 0, p_act = 0, p_seen = 0, p_top = 0, p_bw = 0;
-    auto write_point = [&]() {                        // one thread
-        const size_t p = pt_base + n - 1;
-        tr.xyz[p * 3 + 0] = s[0];
-        tr.xyz[p * 3 + 1] = s[1];
-        tr.xyz[p * 3 + 2] = s[2];
-        tr.val[p] = s_wv[p_bw];
-        tr.nd[p] = s_wd2[p_bw];
-        tr.act[p] = p_act;
-        tr.seen[p] = p_seen;
-        tr.top[p] = p_top;
+    long long pairs = 0, entries = 0;                     // this thread's share (counted by one thread or one lane per step)
+    int steps_here = 0, stop_v = 0, buf = 0, rpar = 0, dpar = 0;
+    bool stop_now = false;
+    enum { STEP = 0, DETOUR = 1, STRAIGHT = 2 };          // how the next step is taken: singly, in a detour batch, in a run
+    int mode = cfg.run_ok ? STRAIGHT : STEP;
+    int singly = 0, wait = 1;                             // single steps left before the next detour batch; their next number
+    // Points [fl, to) from the ring to the trajectory, one per lane of the
+    // calling wave.  A run's point has its goal term for a value (no penalty
+    // reaches it), evaluated here for 64 points at a time instead of once per
+    // step by a whole wave.
+    int fl = n;
+    auto write_points = [&](int from, int to) {
+        const int i = from + lane;
+        if (i >= to) return;
+        const int r = i % RING;
+        const size_t p = pt_base + i;
+        const double x = sP[r][0], y = sP[r][1], z = sP[r][2];
+        const int pa = sPa[r];
+        tr.xyz[p * 3 + 0] = x;
+        tr.xyz[p * 3 + 1] = y;
+        tr.xyz[p * 3 + 2] = z;
+        tr.val[p] = (pa >> 16) ? goal_term(cfg, x, y, z, g) : sPv[r];
+        tr.nd[p] = sPd[r];
+        tr.act[p] = pa & 0xffff;
+        tr.seen[p] = sPs[r];
+        tr.top[p] = sPt[r];
         tr.ep[p] = epoch;
         tr.col[p] = -1;
     };
+    // 64 points at a time; a run's last points may not be visible to the
+    // writing wave before the next barrier: they stay
+    auto flush_points = [&]() {                           // uniform
+        if (n - fl >= 64 + RUN) {
+            if (wave == NW - 1) write_points(fl, fl + 64);
+            fl += 64;
+        }
+    };
+    // the state's component of this lane (x, y, z, x of every four lanes)
+    const int comp = (lane & 3) == 3 ? 0 : lane & 3;
+    const double ell2_hi = cfg.ell * cfg.ell * (1.0 + 1e-9);
+    if (tid < 3) sP[(n - 1) % RING][tid] = s[tid];        // the state a run starts from
+    __syncthreads();
     // scoring rounds q that hold an action of this wave (wave-uniform)
     const int nq = min(APT, max(0, (A - wave * 64 + NT - 1) / NT));
 
@@ -229,7 +303,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         const int t = t0 + k;
         {
             const double ex = g[0] - s[0], ey = g[1] - s[1], ez = g[2] - s[2];
-            if (sqrt(ex * ex + ey * ey + ez * ez) <= cfg.ell) {
+            const double e2 = norm2(ex, ey, ez);
+            if (e2 <= ell2_hi && sqrt(e2) <= cfg.ell) {
                 status = FASTMDP_OK;
                 break;
             }
@@ -237,109 +312,572 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 status = FASTMDP_TIMEOUT;
                 break;
             }
-            if (steps_here >= budget || s_stop) break;    // resumable: stays running
+            if (steps_here >= budget || stop_now) break;  // resumable: stays running
+        }
+        shift_counts(t + 1);
+        flush_points();
+
+        // 0. A run: steps whose choice no plan can change, RUN at a time.
+        //    While no well reaches the goal-directed action's successor
+        //    (heading 0, the fastest speed, the climb nearest the goal's
+        //    altitude), its value is its goal term, and no other action's
+        //    value exceeds its own goal term (the penalties are
+        //    non-negative); so where every other successor is farther from
+        //    the goal by more than run_margin, it is the choice, alone inside
+        //    the tie band.  The states of a batch follow from one another
+        //    without the table: wave 0 computes the next batch's while wave
+        //    1, four lanes per step, checks this batch's actions, box,
+        //    terrain and indexed entries and the other waves its rows' later
+        //    columns, so a batch takes what the chain of its states takes and
+        //    one barrier.  The steps before the first unconfirmed one are
+        //    taken, with the records the single step would leave; that one
+        //    is left to the modes below.
+        if (mode == STRAIGHT) {                           // uniform
+            const int left = min(cfg.max_steps - k, budget - steps_here);
+            // wave 0: the batch p of the states from point n0 - 1 (component
+            // s_l) on, at most lim of them: successors into the ring,
+            // directions and distances into sQ
+            double s_l = comp == 0 ? s[0] : comp == 1 ? s[1] : s[2];
+            const double g_l = comp == 0 ? g[0] : comp == 1 ? g[1] : g[2];
+            const double v_step = sStep[cfg.run_v];
+            auto chain = [&](int p, int n0, int lim) {
+                // the climb, and for how many steps it can stay the best (a
+                // step past that is caught by the check)
+                const double z0 = dpp_bcast_f64<2>(s_l);
+                int cg = 0;
+                double e0 = INFINITY;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const double e = fabs(g[2] - (z0 + sDz[c]));
+                    if (e < e0) {
+                        e0 = e;
+                        cg = c;
+                    }
+                }
+                const double c_dz = sDz[cg];
+                int nb = max(0, min(RUN, lim));
+                if (c_dz != 0.0) {
+                    const float m = (float)fabs(g[2] - z0) / (float)fabs(c_dz);
+                    nb = min(nb, max(1, (int)fminf(m, 1e4f)));
+                }
+                nb = __builtin_amdgcn_readfirstlane(nb);
+                if (lane == 0) {
+                    sNb[p] = nb;
+                    sAg[p] = cg * NV + cfg.run_v;         // heading 0
+                }
+                for (int i = 0; i < nb; ++i) {            // uniform
+                    // one step of all three components: the horizontal
+                    // distance by Goldschmidt's iteration and the quotients
+                    // b / br from the same reciprocal square root with one
+                    // exact remainder each, rounded as the square root and
+                    // the divisions of the single step round (r2 is far from
+                    // the ends of the range: checked with the step)
+                    const double b = g_l - s_l;
+                    const double bx = dpp_bcast_f64<0>(b), by = dpp_bcast_f64<1>(b);
+                    const double r2 = dot2(bx, bx, by, by);
+                    const double y = __builtin_amdgcn_rsq(r2);
+                    double a = r2 * y, h = 0.5 * y;
+                    const double e = __builtin_fma(-h, a, 0.5);
+                    a = __builtin_fma(a, e, a);
+                    h = __builtin_fma(h, e, h);
+                    a = __builtin_fma(__builtin_fma(-a, a, r2), h, a);
+                    const double br = __builtin_fma(__builtin_fma(-a, a, r2), h, a);
+                    const double inv = h + h, q0 = b * inv;
+                    const double q = __builtin_fma(__builtin_fma(-br, q0, b), inv, q0);
+                    s_l = comp == 2 ? s_l + c_dz : __builtin_fma(v_step, q, s_l);
+                    if (lane < 3) {
+                        sQ[p][i][lane] = lane == 2 ? br : q;
+                        sP[(n0 + i) % RING][lane] = s_l;
+                    }
+                }
+            };
+            int par = 0, taken = 0;
+            if (wave == 0) chain(0, n, left);
+            lds_barrier();
+            for (;;) {                                    // uniform
+                const int nb = sNb[par], ag = sAg[par];
+                const int tr0 = t0 + n;                   // row of the batch's first step (t + 1)
+                if (wave == 0) {
+                    chain(par ^ 1, n + nb, left - taken - nb);
+                } else if (wave == 1) {
+                    const int st = lane >> 2, sub = lane & 3;
+                    const int row = tr0 + st;
+                    const bool act = st < nb;
+                    const int idn = act ? row_indexed(row) : 0;
+                    const int r0 = (n + st - 1) % RING, r1 = (n + st) % RING;
+                    const double x = sP[r0][0], y = sP[r0][1], z = sP[r0][2];
+                    // the step's row of cells: its first records are on
+                    // their way during the checks
+                    const int x0 = grid_cell((float)x - g_half, tb.qx0, tb.gsx);
+                    const int x1 = grid_cell((float)x + g_half, tb.qx0, tb.gsx);
+                    int cy = grid_cell((float)y - g_half, tb.qy0, tb.gsy);
+                    const int y1 = grid_cell((float)y + g_half, tb.qy0, tb.gsy);
+                    const int *off = tb.goff + (size_t)row * (kGridCells + 1);
+                    const float4 *rec = tb.grec + (size_t)row * tb.cap;
+                    int a = 0, b = 0;
+                    if (idn > 0) {
+                        a = off[cy * kGrid + x0];
+                        b = off[cy * kGrid + x1 + 1];
+                    }
+                    const double nx = sP[r1][0], ny = sP[r1][1], nz = sP[r1][2];
+                    const double cb = sQ[par][st][0], sb = sQ[par][st][1], br = sQ[par][st][2];
+                    bool good = act && !outside_box(cfg, nx, ny, nz);
+                    const double bx = g[0] - x, by = g[1] - y, bz = g[2] - z;
+                    const double r2 = dot2(bx, bx, by, by), e2 = __builtin_fma(bz, bz, r2);
+                    const double far = br + fabs(bz);     // at least the state's distance to the goal
+                    good = good && far <= cfg.run_dmax && e2 > ell2_hi && r2 > 1e-100;
+                    {
+                        const double ex = g[0] - nx, ey = g[1] - ny, ez = g[2] - nz;
+                        const double d2g = norm2(ex, ey, ez);
+                        const double lim = d2g * (1.0 + 1e-14) + cfg.run_margin * (2.0 * far + cfg.run_margin) * 1.0001;
+                        // heading 0's actions exactly as scored, and the
+                        // nearest that any other heading's can come
+#pragma unroll
+                        for (int i = 0; i < (NC * NV + 3) / 4; ++i) {
+                            const int q = min(sub + 4 * i, NC * NV - 1);
+                            const double stp = sStep[q % NV];
+                            const double fx = g[0] - __builtin_fma(stp, cb, x), fy = g[1] - __builtin_fma(stp, sb, y);
+                            const double fz = g[2] - (z + sDz[q / NV]);
+                            const double fz2 = fz * fz;
+                            const double d2h = norm2(fx, fy, fz);
+                            const double d2o = r2 + stp * (stp - 2.0 * br * cfg.run_c1) + fz2 - (1e-6 + 1e-12 * r2);
+                            good = good && (q == ag || d2h > lim) && d2o > lim;
+                        }
+                    }
+                    if (tb.terr) good = good && nz - terrain_height(tb, nx, ny) >= cfg.R_terr;
+                    // the indexed entries near the state, every fourth of its
+                    // cells' records
+                    const float ch = (float)cb, sh = (float)sb, kvv = sKv[cfg.run_v], clv = sClf[ag / NV];
+                    int nkeep = 0;
+                    float m = INFINITY;
+                    a += sub;
+                    while (__ballot(a < b || (idn > 0 && cy < y1))) {       // uniform
+                        if (a < b) {
+                            float4 e;
+                            if (near_entry(rec[a], x, y, z, e)) {
+                                const float hq = fmaf(e.x, ch, e.y * sh);
+                                const float uu = fmaf(kvv, hq, e.w);
+                                m = fminf(m, ag / NV == ZC ? uu : fmaf(clv, e.z, uu));
+                                nkeep += 1;
+                            }
+                            a += 4;
+                        } else if (idn > 0 && cy < y1) {
+                            cy += 1;
+                            a = off[cy * kGrid + x0] + sub;
+                            b = off[cy * kGrid + x1 + 1];
+                        }
+                    }
+                    m = fminf(m, dpp_f32<kDppQuad1032>(m));
+                    m = fminf(m, dpp_f32<kDppQuad2301>(m));
+                    nkeep += dpp_i32<kDppQuad1032>(nkeep);
+                    nkeep += dpp_i32<kDppQuad2301>(nkeep);
+                    const uint64_t gb = __ballot(good);
+                    if (sub == 0) {
+                        sMg[par][st] = m;
+                        sNg[par][st] = nkeep;
+                        sOk[par][st] = (gb >> (4 * st) & 15u) == 15u;
+                    }
+                    if (lane == 0 && stop.target > 0) {
+                        stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        s_stop_run[par] = stop_v >= stop.target;
+                    }
+                } else {
+                    for (int st = wave - 2; st < nb; st += NW - 2) {        // uniform per wave
+                        const int row = tr0 + st, n_row = row_count(row), idn = row_indexed(row);
+                        int nkeep = 0;
+                        float m = INFINITY;
+                        if (idn < n_row) {
+                            const int r0 = (n + st - 1) % RING;
+                            const double x = sP[r0][0], y = sP[r0][1], z = sP[r0][2];
+                            const float ch = (float)sQ[par][st][0], sh = (float)sQ[par][st][1];
+                            const float kvv = sKv[cfg.run_v], clv = sClf[ag / NV];
+                            const size_t rb = (size_t)row * tb.cap;
+                            const u16x2 corner = q_corner(x, y, q_half);
+                            for (int base = idn & ~3; base < n_row; base += 4 * 256) {   // uniform per wave
+                                uint4 q[4];
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) {
+                                    const int j = base + 256 * u + 4 * lane;
+                                    q[u] = make_uint4(0u, 0u, 0u, 0u);
+                                    if (j < n_row) q[u] = *reinterpret_cast<const uint4 *>(tb.Q + rb + j);
+                                }
+                                uint32_t cm = 0u;
+#pragma unroll
+                                for (int u = 0; u < 4; ++u)
+                                    if (base + 256 * u < n_row)             // uniform per wave
+                                        cm |= q_inside(q[u], corner, q_width, base + 256 * u + 4 * lane, idn, n_row) << (4 * u);
+                                while (__ballot(cm != 0u)) {                // uniform per wave
+                                    bool keep = false;
+                                    if (cm) {
+                                        const int bit = __builtin_ctz(cm);
+                                        cm &= cm - 1u;
+                                        float4 e;
+                                        keep = near_entry(table_entry(rb + base + 256 * (bit >> 2) + 4 * lane + (bit & 3)),
+                                                          x, y, z, e);
+                                        if (keep) {
+                                            const float hq = fmaf(e.x, ch, e.y * sh);
+                                            const float uu = fmaf(kvv, hq, e.w);
+                                            m = fminf(m, ag / NV == ZC ? uu : fmaf(clv, e.z, uu));
+                                        }
+                                    }
+                                    nkeep += __popcll(__ballot(keep));
+                                }
+                            }
+                            if (nkeep) m = wave_min_f32(m);
+                        }
+                        if (lane == 0) {
+                            sMt[par][st] = m;
+                            sNt[par][st] = nkeep;
+                        }
+                    }
+                }
+                lds_barrier();
+                // one lane per step: the nearest plan of its successor, and
+                // whether the step stands
+                const int st = lane & (RUN - 1);
+                const int nk = sNg[par][st] + sNt[par][st];
+                const float m = fminf(sMg[par][st], sMt[par][st]);
+                const double d2n = nk > 0 ? nearest_d2<NC, NV>(at, ag, m) : INFINITY;
+                const uint64_t undecided = __ballot(st >= nb || !sOk[par][st] || !(d2n >= cfg.band_hi2));
+                const int f = min(nb, undecided ? __builtin_ctzll(undecided) : RUN);       // steps taken
+                if (wave == 0 && lane < f) {
+                    const int ri = (n + lane) % RING, cnt = row_count(tr0 + lane);
+                    sPd[ri] = d2n;
+                    sPa[ri] = ag | 1 << 16;
+                    sPs[ri] = cnt;
+                    sPt[ri] = -1;
+                    pairs += (long long)A * nk;
+                    entries += cnt;
+                }
+                stop_now = stop.target > 0 && s_stop_run[par];
+                n += f;
+                steps_here += f;
+                taken += f;
+                par ^= 1;
+                if (f < nb) mode = cfg.detour_ok ? DETOUR : STEP;
+                if (f < nb || stop_now || sNb[par] == 0) break;
+                shift_counts(t0 + n);
+                flush_points();
+            }
+            const int ri = (n - 1) % RING;
+            s[0] = sP[ri][0]; s[1] = sP[ri][1]; s[2] = sP[ri][2];
+            lds_barrier();                                // the last batch is read before the next run writes its own
+            continue;
+        }
+
+        // 0b. A detour batch: up to DS steps among the plans near them, one
+        //    barrier each.  An action outside every well has its goal term
+        //    for a value (terrain aside) and beats every action inside one
+        //    (detour_ok), so the choice is the action nearest the goal among
+        //    those outside, where no other of them comes as near to within
+        //    run_margin.  The entries within reach of the batch's states
+        //    (each lies within the steps taken so far of the first) are
+        //    listed first, one row per wave at a time; each step then reads
+        //    no memory and evaluates no exponential.  Whatever this rule does
+        //    not decide (no action outside the wells, a tie, terrain within
+        //    reach) is left to the single step below.
+        if (mode == DETOUR) {                             // uniform
+            if (tid == 0 && stop.target > 0)
+                stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int kb = min(DS, min(cfg.max_steps - k, budget - steps_here));
+#pragma unroll
+            for (int i = 0; i < DS / NW; ++i) {
+                const int kk = wave + NW * i;             // the row of step kk
+                if (kk >= kb) continue;                   // uniform per wave
+                const int row = t + 1 + kk, n_row = row_count(row), idn = row_indexed(row);
+                const size_t rb = (size_t)row * tb.cap;
+                const float reach = cfg.cull_box + 1.0f + (float)kk * (float)cfg.max_step;
+                int cnt = 0;
+                auto list = [&](bool have, const float4 p) {
+                    float4 e;
+                    near_entry(p, s[0], s[1], s[2], e);
+                    const bool keep = have && __float_as_int(p.w) < seq && e.w < reach * reach;
+                    const uint64_t bal = __ballot(keep);
+                    const int at_i = cnt + lanes_below(bal);
+                    if (keep && at_i < DL) sList[kk][at_i] = p;
+                    cnt += __popcll(bal);
+                };
+                if (idn > 0) {
+                    const Cells cl = cells((float)s[0], (float)s[1], reach);
+                    for (int cy = cl.y0; cy <= cl.y1; cy += 2) {            // uniform
+                        int a, b;
+                        cell_range(row, cl, cy, a, b);
+                        for (a += lane & 31; __ballot(a < b); a += 32) {    // uniform per wave
+                            float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            if (a < b) p = tb.grec[rb + a];
+                            list(a < b, p);
+                        }
+                    }
+                }
+                if (idn < n_row) {
+                    const u16x2 half = q_half + __builtin_bit_cast(u16x2, cfg.run_step) * (uint16_t)kk;
+                    const u16x2 corner = q_corner(s[0], s[1], half);
+                    for (int base = idn & ~3; base < n_row; base += 256) {  // uniform
+                        const int j = base + 4 * lane;
+                        uint4 q = make_uint4(0u, 0u, 0u, 0u);
+                        if (j < n_row) q = *reinterpret_cast<const uint4 *>(tb.Q + rb + j);
+                        uint32_t cm = q_inside(q, corner, half + half, j, idn, n_row);
+                        while (__ballot(cm != 0u)) {      // uniform per wave
+                            const bool have = cm != 0u;
+                            float4 p = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                            if (have) {
+                                p = table_entry(rb + j + __builtin_ctz(cm));
+                                cm &= cm - 1u;
+                            }
+                            list(have, p);
+                        }
+                    }
+                }
+                if (lane == 0) sListN[kk] = cnt;
+            }
+            if (tid == 0) s_stop_run[0] = stop.target > 0 && stop_v >= stop.target;
+            lds_barrier();
+            stop_now = s_stop_run[0];
+            double x = s[0], y = s[1], z = s[2];
+            int f = 0, direct = 0;
+            for (; f < kb; ++f) {                         // uniform: every wave decides alike
+                mode = STEP;
+                const int cnt = sListN[f];
+                if (cnt > DL) break;
+                // this state's entries, one per lane
+                float4 e = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
+                bool keep = false;
+                if (lane < cnt) keep = near_entry(sList[f][lane], x, y, z, e);
+                const uint64_t near = __ballot(keep);
+                const double bx = g[0] - x, by = g[1] - y, bz = g[2] - z;
+                const double r2 = dot2(bx, bx, by, by), e2 = __builtin_fma(bz, bz, r2);
+                // the direction, as a run's chain has it
+                const double yq = __builtin_amdgcn_rsq(r2);
+                double aq = r2 * yq, hq2 = 0.5 * yq;
+                const double eq = __builtin_fma(-hq2, aq, 0.5);
+                aq = __builtin_fma(aq, eq, aq);
+                hq2 = __builtin_fma(hq2, eq, hq2);
+                aq = __builtin_fma(__builtin_fma(-aq, aq, r2), hq2, aq);
+                const double br = __builtin_fma(__builtin_fma(-aq, aq, r2), hq2, aq);
+                const double inv = hq2 + hq2;
+                const double cx0 = bx * inv, sx0 = by * inv;
+                const double cb = __builtin_fma(__builtin_fma(-br, cx0, bx), inv, cx0);
+                const double sb = __builtin_fma(__builtin_fma(-br, sx0, by), inv, sx0);
+                const double far = br + fabs(bz);
+                if (!(e2 > ell2_hi && r2 > 1e-100 && far <= cfg.run_dmax)) break;
+                // this thread's actions: squared distance to the goal, and
+                // infinity inside a well (or out of the box)
+                const double xyz[3] = {x, y, z};
+                double b1 = INFINITY, b2 = INFINITY, bn = INFINITY, qx = x, qy = y, qz = z;
+                int ba = 0;
+#pragma unroll
+                for (int q = 0; q < APT; ++q) {
+                    if (wave * 64 + q * NT >= A) continue;                  // uniform per wave
+                    const int a = min(tid + q * NT, A - 1), h = a / (NC * NV), c = (a / NV) % NC, v = a % NV;
+                    const double dx = dot2(cb, sC0[h], -sb, sS0[h]), dy = dot2(sb, sC0[h], cb, sS0[h]);
+                    double px, py, pz;
+                    successor(cfg, at, a, xyz, dx, dy, px, py, pz);
+                    const double ex = g[0] - px, ey = g[1] - py, ez = g[2] - pz;
+                    double d2 = norm2(ex, ey, ez);
+                    const float ch = (float)dx, sh = (float)dy, kvv = sKv[v], clv = sClf[c];
+                    float m = INFINITY;
+                    for (uint64_t nb = near; nb; nb &= nb - 1) {            // uniform
+                        const int l = __builtin_ctzll(nb);
+                        const float ux = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e.x), l));
+                        const float uy = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e.y), l));
+                        const float uz = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e.z), l));
+                        const float uw = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(e.w), l));
+                        const float hq = fmaf(ux, ch, uy * sh);
+                        const float uu = fmaf(kvv, hq, uw);
+                        m = fminf(m, c == ZC ? uu : fmaf(clv, uz, uu));
+                    }
+                    const double dn = nearest_d2<NC, NV>(at, a, m);
+                    if (tid + q * NT >= A || outside_box(cfg, px, py, pz) || dn <= cfg.band_lo2) d2 = INFINITY;
+                    const bool less = d2 < b1;
+                    b2 = fmin(b2, less ? b1 : d2);
+                    if (less) {
+                        b1 = d2;
+                        bn = dn;
+                        ba = a;
+                        qx = px;
+                        qy = py;
+                        qz = pz;
+                    }
+                }
+                // the wave's nearest, then the workgroup's
+                const double slack = cfg.run_margin * (2.0 * (far + cfg.max_step) + cfg.run_margin) * 1.0001;
+                {
+                    const double d1 = -wave_max(-b1);
+                    const double lim = d1 * (1.0 + 1e-14) + slack;
+                    const uint64_t first = __ballot(b1 == d1), close = __ballot(b1 <= lim), second = __ballot(b2 <= lim);
+                    if (lane == __builtin_ctzll(first)) {
+                        sR[dpar][wave][0] = d1;
+                        sR[dpar][wave][1] = qx;
+                        sR[dpar][wave][2] = qy;
+                        sR[dpar][wave][3] = qz;
+                        sR[dpar][wave][4] = bn;
+                        sRa[dpar][wave] = ba;
+                        sRn[dpar][wave] = __popcll(close) + __popcll(second);
+                    }
+                }
+                lds_barrier();
+                double d1 = INFINITY;
+                int w1 = 0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    const double d = sR[dpar][w][0];
+                    if (d < d1) {
+                        d1 = d;
+                        w1 = w;
+                    }
+                }
+                const double lim = d1 * (1.0 + 1e-14) + slack;
+                int close = 0;
+#pragma unroll
+                for (int w = 0; w < NW; ++w) close += w != w1 && sR[dpar][w][0] <= lim;
+                const int best = sRa[dpar][w1];
+                const double px = sR[dpar][w1][1], py = sR[dpar][w1][2], pz = sR[dpar][w1][3];
+                double dn = sR[dpar][w1][4];
+                const bool alone = d1 < INFINITY && close == 0 && sRn[dpar][w1] == 1;
+                dpar ^= 1;
+                if (!alone) break;
+                if (dn < cfg.band_hi2) {
+                    // within kBand of the radius: the nearest distance in
+                    // FP64 over the entries in reach, as the single step has it
+                    double dd = INFINITY;
+                    if (keep) {
+                        const float4 p = sList[f][lane];
+                        dd = entry_d2(px, py, pz, p.x, p.y, p.z);
+                    }
+                    dn = -wave_max(-dd);
+                    if (!(dn >= cfg.R_intr * cfg.R_intr)) break;
+                }
+                if (tb.terr && !(pz - terrain_height(tb, px, py) >= cfg.R_terr)) break;
+                mode = DETOUR;
+                if (tid == 0) {
+                    const int ri = n % RING, rc = row_count(t + 1 + f);
+                    sP[ri][0] = px;
+                    sP[ri][1] = py;
+                    sP[ri][2] = pz;
+                    sPd[ri] = dn;
+                    sPa[ri] = best | 1 << 16;
+                    sPs[ri] = rc;
+                    sPt[ri] = -1;
+                    pairs += (long long)A * __popcll(near);
+                    entries += rc;
+                }
+                // back to runs once two choices in a row were the goal-directed one
+                {
+                    double ez = INFINITY;
+                    int cg = 0;
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) {
+                        const double d = fabs(g[2] - (z + sDz[c]));
+                        if (d < ez) {
+                            ez = d;
+                            cg = c;
+                        }
+                    }
+                    direct = best == cg * NV + cfg.run_v ? direct + 1 : 0;
+                }
+                x = px; y = py; z = pz;
+                n += 1;
+                if (direct >= 2) {
+                    mode = STRAIGHT;
+                    ++f;
+                    break;
+                }
+            }
+            s[0] = x; s[1] = y; s[2] = z;
+            steps_here += f;
+            if (f > 0) wait = 1;
+            if (mode == STEP) {                           // undecided: single steps, more of them each time in a row
+                singly = wait;
+                wait = min(2 * wait, 16);
+            }
+            lds_barrier();                                // the lists are read before the next batch writes its own
+            continue;
         }
 
         // heading directions: the goal bearing rotated by each offset
         {
             const double bx = g[0] - s[0], by = g[1] - s[1];
-            const double br = sqrt(bx * bx + by * by);
+            const double br = sqrt(dot2(bx, bx, by, by));
             const double cb = br > 0.0 ? bx / br : 1.0, sb = br > 0.0 ? by / br : 0.0;
             if (tid < H) {
-                sCos[buf][tid] = cb * c0 - sb * s0;
-                sSin[buf][tid] = sb * c0 + cb * s0;
+                sCos[buf][tid] = dot2(cb, sC0[tid], -sb, sS0[tid]);
+                sSin[buf][tid] = dot2(sb, sC0[tid], cb, sS0[tid]);
             }
         }
         const double *hc = sCos[buf], *hs = sSin[buf];
         const int row = t + 1;
-        const int n_row = pre_n;
-        entries += n_row;                                 // (thread 0's count is the one kept)
+        const int n_row = row_count(row);
+        if (tid == 0) entries += n_row;
         const size_t rb = (size_t)row * tb.cap;
         int n_vis = 0;
         float mA[APT];
 #pragma unroll
         for (int i = 0; i < APT; ++i) mA[i] = INFINITY;
-        const float sx = (float)s[0], sy = (float)s[1];
-        // the count of the row after next and the launch stop counter, read
-        // once this wave's loads of the row have landed (the wait for them
-        // then does not include these reads) and in flight through the rest
-        // of the step
-        int nn_after = 0;
-        auto read_ahead = [&]() {
-            nn_after = row_count(row + 2);
-            if (tid == 0 && stop.target > 0)
-                stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        };
-        if (n_row == 0) read_ahead();
+        if (tid == 0 && stop.target > 0)
+            stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-        int par = 0;                                      // alternate s_rem buffer (see below)
-        for (int base = 0; base < n_row; base += RAW) {  // uniform
-            if (base > 0) load_xy(row, base, n_row);     // chunks after the first: loaded here
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's loads of the chunk landed
-            if (base == 0) read_ahead();
-            const int lim = min(n_row - base, RAW);
-            // 1. box test of this lane's entries: bit 4 i + m of cm marks
-            //    entry 4 tid + 4 NT i + m of the chunk
-            uint32_t cm = 0u;
-#pragma unroll
-            for (int i = 0; i < G4; ++i) {
-                const int j = 4 * tid + i * 4 * NT;
-                const float4 x4 = *reinterpret_cast<const float4 *>(rawX + j);
-                const float4 y4 = *reinterpret_cast<const float4 *>(rawY + j);
-                const float xs[4] = {x4.x, x4.y, x4.z, x4.w};
-                const float ys[4] = {y4.x, y4.y, y4.z, y4.w};
-                uint32_t g4 = 0u;
-#pragma unroll
-                for (int m = 0; m < 4; ++m)
-                    g4 |= (fmaxf(fabsf(xs[m] - sx), fabsf(ys[m] - sy)) <= cbox ? 1u : 0u) << m;
-                const int r = lim - j;                    // entries of the group inside the chunk
-                cm |= (r >= 4 ? g4 : (r > 0 ? g4 & ((1u << r) - 1u) : 0u)) << (4 * i);
+        // 1. the row's entries near the state, one per lane and round: the
+        //    records of the cells around it (wave 0) and the later columns
+        //    inside the 16-bit box (groups of 256 dealt to the waves, 8 * NW
+        //    of them per pass), by the exact test; staged, then swept by
+        //    every thread for its actions
+        if (n_row > 0) {
+            const int idn = row_indexed(row);
+            const Cells cl = cells((float)s[0], (float)s[1], g_half);
+            const u16x2 corner = q_corner(s[0], s[1], q_half);
+            int cy = cl.y0, ia = 0, ib = 0;
+            if (wave == 0 && idn > 0) {
+                cell_range(row, cl, cy, ia, ib);
+                ia += lane & 31;
             }
-            // the flags of remaining candidates alternate between two
-            // buffers: a buffer is rewritten only after a barrier that
-            // follows every read of its previous contents
-            const uint64_t any0 = __ballot(cm != 0u);
-            par ^= 1;
-            if (lane == 0) s_rem[par][wave] = any0 != 0;
-            lds_barrier();                                // also: this step's heading directions visible
-            bool more = false;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) more = more || s_rem[par][w];
-            // 2. the candidates, one per lane and round: exact test, staging,
-            //    sweep of the staged entries
+            int base = idn & ~3;                          // the next pass over the later columns
+            uint32_t cm = 0u;
+            int cbase = 0;
+            bool more = true;
+            int par = 0;                                  // alternate s_rem buffer (see below)
             while (more) {                                // uniform
+                // a pass's candidates: bit 4 i + m of cm marks column cbase +
+                // 256 NW i + m
+                if (!__ballot(cm != 0u) && base < n_row) {                 // uniform per wave
+                    cbase = base + 256 * wave + 4 * lane;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const int j = cbase + 256 * NW * i;
+                        if (base + 256 * (wave + NW * i) < n_row) {        // uniform per wave
+                            uint4 q = make_uint4(0u, 0u, 0u, 0u);
+                            if (j < n_row) q = *reinterpret_cast<const uint4 *>(tb.Q + rb + j);
+                            cm |= q_inside(q, corner, q_width, j, idn, n_row) << (4 * i);
+                        }
+                    }
+                    base += 8 * 256 * NW;
+                }
                 bool keep = false;
                 float4 e = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
-                if (cm) {
+                if (ia < ib) {
+                    keep = near_entry(tb.grec[rb + ia], s[0], s[1], s[2], e);
+                    ia += 32;
+                } else if (cm) {
                     const int bit = __builtin_ctz(cm);
                     cm &= cm - 1u;
-                    const int jj = 4 * tid + (bit >> 2) * 4 * NT + (bit & 3);
-                    const size_t idx = rb + base + jj;
-                    const float xs = rawX[jj], ys = rawY[jj];   // the DMA's copy of X, Y at idx
-                    float zs;
-                    int kv;
-                    if constexpr (ZV) {
-                        zs = rawZ[jj];
-                        kv = rawV[jj];
-                    } else {
-                        zs = tb.Z[idx];
-                        kv = tb.vis[idx];
-                    }
-                    const float qx = (float)((double)xs - s[0]);
-                    const float qy = (float)((double)ys - s[1]);
-                    const float qz = (float)((double)zs - s[2]);
-                    const float w = fmaf(qx, qx, fmaf(qy, qy, qz * qz));
-                    e = make_float4(qx, qy, cfg.zeta_scale * qz, w);
-                    keep = kv < seq && w < cfg.cull_r2;
+                    keep = near_entry(table_entry(rb + cbase + 256 * NW * (bit >> 2) + (bit & 3)), s[0], s[1], s[2], e);
+                }
+                if (wave == 0 && idn > 0 && !__ballot(ia < ib) && cy + 2 <= cl.y1) {   // the next rows of cells
+                    cy += 2;
+                    cell_range(row, cl, cy, ia, ib);
+                    ia += lane & 31;
                 }
                 const uint64_t kb = __ballot(keep);
-                const uint64_t rem = __ballot(cm != 0u);
+                const bool rem = __ballot(cm != 0u || ia < ib) || base < n_row ||
+                                 (wave == 0 && idn > 0 && cy + 2 <= cl.y1);
                 par ^= 1;
                 if (lane == 0) {
                     s_wsum[wave] = __popcll(kb);
-                    s_rem[par][wave] = rem != 0;
+                    s_rem[par][wave] = rem;
                 }
-                lds_barrier();
+                // the flags of remaining candidates alternate between two
+                // buffers: a buffer is rewritten only after a barrier that
+                // follows every read of its previous contents
+                lds_barrier();                            // also: this step's heading directions visible
                 int tp = 0, tn = 0;
                 more = false;
 #pragma unroll
@@ -376,12 +914,6 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
             }
         }
         if (n_row == 0) lds_barrier();                    // heading directions visible
-        // the next step's row, in flight during the valuation (this lane's
-        // slots of the chunk are read)
-        pre_n = nn;
-        if (pre_n > 0) load_xy(row + 1, 0, pre_n);
-        nn = nn_after;
-
         // 3. per-action value in FP64 (the 1024-thread kernel's scoring);
         //    actions whose nearest distance lies within kBand of the well
         //    radius get it recomputed exactly first.  Kept per action: value,
@@ -425,10 +957,6 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         if (nq >= APT) score_rounds(std::integral_constant<int, APT>());
         else if (nq == 1) score_rounds(std::integral_constant<int, 1>());
         else score_rounds(std::integral_constant<int, 0>());
-        if (pend) {                                       // uniform
-            if (tid == NT - 64) write_point();            // the previous step's point (see above)
-            pend = 0;
-        }
         double wv = wave_max(vloc);
         if (lane == 0) red_d[wave] = wv;
         if (mine_band) s_any = 1;
@@ -509,6 +1037,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
             }
         if (tid == 0 && stop.target > 0) s_stop = stop_v >= stop.target;
         lds_barrier();
+        stop_now = s_stop;
         int best = 0x7fffffff, top = 0x7fffffff, bw = 0;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
@@ -530,11 +1059,34 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
             successor(cfg, at, best, s, hc[h], hs[h], x, y, z);
             const int flb = s_wfl[bw];
             if (tid == 0) pairs += (long long)A * n_vis;  // pairs with the plans this request sees
-            pend = 1;
-            p_act = best;
-            p_seen = n_row;
-            p_top = top != best ? top : -1;
-            p_bw = bw;
+            if (tid == 0) {
+                const int ri = n % RING;
+                sP[ri][0] = x;
+                sP[ri][1] = y;
+                sP[ri][2] = z;
+                sPv[ri] = s_wv[bw];
+                sPd[ri] = s_wd2[bw];
+                sPa[ri] = best;
+                sPs[ri] = n_row;
+                sPt[ri] = top != best ? top : -1;
+            }
+            // the goal-directed action was the choice: the next steps may be
+            // a run; else a detour batch, unless those decided nothing lately
+            if (cfg.run_ok) {
+                double ez = INFINITY;
+                int cg = 0;
+#pragma unroll
+                for (int c = 0; c < NC; ++c) {
+                    const double e = fabs(g[2] - (s[2] + sDz[c]));
+                    if (e < ez) {
+                        ez = e;
+                        cg = c;
+                    }
+                }
+                singly -= singly > 0;
+                if (best == cg * NV + cfg.run_v) mode = STRAIGHT;
+                else if (cfg.detour_ok && singly == 0) mode = DETOUR;
+            }
             s[0] = x; s[1] = y; s[2] = z;
             n += 1;
             if (flb & 1) status = FASTMDP_REJECT_SEPARATION;
@@ -546,7 +1098,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         buf ^= 1;
         steps_here += 1;
     }
-    if (pend && tid == NT - 64) write_point();      // the last step's point
+    __syncthreads();   // the last points' records visible
+    for (int i = fl + 64 * wave; i < n; i += 64 * NW) write_points(i, n);
     __syncthreads();   // the trajectory complete for every thread
 
     // Commit validation (shared with the 1024-thread kernel)
@@ -555,12 +1108,14 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         if (tid == 0) S.valid = bad == 0;
     }
 
+    if (pairs > 0 || entries > 0) {
+        atomicAdd(reinterpret_cast<unsigned long long *>(&S.pairs), (unsigned long long)pairs);
+        atomicAdd(reinterpret_cast<unsigned long long *>(&S.entries), (unsigned long long)entries);
+    }
     if (tid == 0) {
         S.n_points = n;
         S.status = status;
         if (stop.target > 0 && status != kRunning) atomicAdd(stop.ctr, 1);
-        S.pairs += pairs;
-        S.entries += entries;
         S.steps += steps_here;
     }
 }

@@ -12,6 +12,16 @@
 
 namespace fmdp {
 
+// Sums of products with their rounding written out: left to the compiler,
+// which product is fused differs from one kernel to the next, and their
+// trajectories by a unit in the last place.
+__device__ __forceinline__ double dot2(double ax, double bx, double ay, double by) {
+    return __builtin_fma(ax, bx, ay * by);
+}
+__device__ __forceinline__ double norm2(double x, double y, double z) {
+    return __builtin_fma(z, z, dot2(x, x, y, y));
+}
+
 __device__ __forceinline__ bool outside_box(const DevCfg &c, double x, double y, double z) {
     return x < c.box_lo[0] || x > c.box_hi[0] || y < c.box_lo[1] || y > c.box_hi[1] ||
            z < c.box_lo[2] || z > c.box_hi[2];
@@ -52,8 +62,8 @@ __device__ __forceinline__ void successor(const DevCfg &c, const ActTab &at, int
     const int v = a % c.n_speed;
     const int cl = (a / c.n_speed) % c.n_climb;
     const double step = at.step[v];
-    x = s[0] + step * dx;
-    y = s[1] + step * dy;
+    x = __builtin_fma(step, dx, s[0]);
+    y = __builtin_fma(step, dy, s[1]);
     z = s[2] + at.dz[cl];
 }
 
@@ -64,9 +74,9 @@ __device__ __forceinline__ void window_point(const DevCfg &c, const ActTab &at, 
     const int cl = (a / c.n_speed) % c.n_climb;
     const double k = (double)w;
     const double step = k * at.step[v];
-    x = s[0] + step * dx;
-    y = s[1] + step * dy;
-    z = s[2] + k * at.dz[cl];
+    x = __builtin_fma(step, dx, s[0]);
+    y = __builtin_fma(step, dy, s[1]);
+    z = __builtin_fma(k, at.dz[cl], s[2]);
 }
 
 // Goal peak r_goal * gamma^(d/ell) at a successor.  Every action's value is
@@ -74,7 +84,7 @@ __device__ __forceinline__ void window_point(const DevCfg &c, const ActTab &at, 
 // proposal certificate rests on; both use this one function.
 __device__ __forceinline__ double goal_term(const DevCfg &c, double x, double y, double z, const double g[3]) {
     const double ex = g[0] - x, ey = g[1] - y, ez = g[2] - z;
-    return c.abs_r_goal * exp(c.log_gamma * (sqrt(ex * ex + ey * ey + ez * ez) / c.ell));
+    return c.abs_r_goal * exp(c.log_gamma * (sqrt(norm2(ex, ey, ez)) / c.ell));
 }
 
 // Squared distance from action a's successor to the nearest plan, from the

@@ -53,9 +53,78 @@ __global__ void scatter_points_kernel(DevTable tb, const float *pts, const int *
     tb.X[idx] = pts[3 * i + 0];
     tb.Y[idx] = pts[3 * i + 1];
     tb.Z[idx] = pts[3 * i + 2];
+    if (tb.Q) tb.Q[idx] = quantised(tb, pts[3 * i + 0], pts[3 * i + 1]);
     tb.vis[idx] = own;
     tb.own[idx] = own;
     tb.dead[idx] = kAlive;
+}
+
+// One workgroup per row.
+__global__ void quantise_table_kernel(DevTable tb) {
+    const int row = blockIdx.x, n = min(tb.rowN[row], tb.cap);
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+        const size_t idx = (size_t)row * tb.cap + j;
+        tb.Q[idx] = quantised(tb, tb.X[idx], tb.Y[idx]);
+    }
+}
+
+// One workgroup per row: the indexed prefix, a histogram of its cells, their
+// offsets, then the records (a cell's in any order: the planner takes a
+// minimum and a count over them).
+constexpr int kGridThreads = 256;
+
+__global__ __launch_bounds__(kGridThreads) void build_grid_kernel(DevTable tb, int limit) {
+    __shared__ int cell_n[kGridCells], part[kGridThreads], s_np;
+    const int row = blockIdx.x, tid = threadIdx.x;
+    const int n = min(tb.rowN[row], tb.cap);
+    const size_t rb = (size_t)row * tb.cap;
+    if (tid == 0) s_np = n;
+    for (int c = tid; c < kGridCells; c += kGridThreads) cell_n[c] = 0;
+    __syncthreads();
+    if (n >= kGridMin) {
+        int np = n;
+        for (int j = tid; j < n; j += kGridThreads)
+            if (tb.vis[rb + j] != kAlive && tb.own[rb + j] >= limit) np = min(np, j);
+        if (np < n) atomicMin(&s_np, np);
+    }
+    __syncthreads();
+    const int np = s_np >= kGridMin ? s_np : 0;
+    if (tid == 0) tb.gn[row] = np;
+    if (np == 0) return;                                     // uniform
+    auto cell = [&](size_t idx) {
+        return grid_cell(tb.Y[idx], tb.qy0, tb.gsy) * kGrid + grid_cell(tb.X[idx], tb.qx0, tb.gsx);
+    };
+    for (int j = tid; j < np; j += kGridThreads)
+        if (tb.vis[rb + j] != kAlive) atomicAdd(&cell_n[cell(rb + j)], 1);
+    __syncthreads();
+    constexpr int PER = kGridCells / kGridThreads;           // cells per thread
+    int mine[PER], sum = 0;
+    for (int i = 0; i < PER; ++i) {
+        mine[i] = sum;
+        sum += cell_n[tid * PER + i];
+    }
+    part[tid] = sum;
+    __syncthreads();
+    for (int d = 1; d < kGridThreads; d <<= 1) {
+        const int v = tid >= d ? part[tid - d] : 0;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    int *off = tb.goff + (size_t)row * (kGridCells + 1);
+    for (int i = 0; i < PER; ++i) {
+        const int o = part[tid] - sum + mine[i];
+        cell_n[tid * PER + i] = o;
+        off[tid * PER + i] = o;
+    }
+    if (tid == kGridThreads - 1) off[kGridCells] = part[tid];
+    __syncthreads();
+    for (int j = tid; j < np; j += kGridThreads) {
+        const int v = tb.vis[rb + j];
+        if (v == kAlive) continue;
+        const int p = atomicAdd(&cell_n[cell(rb + j)], 1);
+        tb.grec[rb + p] = make_float4(tb.X[rb + j], tb.Y[rb + j], tb.Z[rb + j], __int_as_float(v));
+    }
 }
 
 // Plans appended in order from one staging buffer, by one workgroup: plan j
@@ -78,6 +147,7 @@ __global__ __launch_bounds__(1024) void append_plans_kernel(DevTable tb, const i
             tb.X[idx] = p[0];
             tb.Y[idx] = p[1];
             tb.Z[idx] = p[2];
+            if (tb.Q) tb.Q[idx] = quantised(tb, p[0], p[1]);
             tb.vis[idx] = -1;
             tb.own[idx] = -1;
             tb.dead[idx] = kAlive;
@@ -123,6 +193,7 @@ __global__ void commit_append_kernel(DevTable tb, const double *pts, int t0, int
     tb.X[idx] = (float)pts[3 * k + 0];
     tb.Y[idx] = (float)pts[3 * k + 1];
     tb.Z[idx] = (float)pts[3 * k + 2];
+    if (tb.Q) tb.Q[idx] = quantised(tb, (float)pts[3 * k + 0], (float)pts[3 * k + 1]);
     tb.vis[idx] = own;
     tb.own[idx] = own;
     tb.dead[idx] = kAlive;
@@ -194,6 +265,7 @@ __global__ __launch_bounds__(kPassThreads) void fcfs_insert_kernel(DevTable tb, 
         tb.X[idx] = (float)x[0];
         tb.Y[idx] = (float)x[1];
         tb.Z[idx] = (float)x[2];
+        if (tb.Q) tb.Q[idx] = quantised(tb, (float)x[0], (float)x[1]);
         tb.vis[idx] = own;
         tb.own[idx] = own;
         tb.dead[idx] = kAlive;
@@ -815,6 +887,16 @@ hipError_t launch_fcfs_abort(const DevTable &t, Slot *slots, const int *list, in
 hipError_t launch_fill_int(int *p, int value, int n, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_int_kernel, dim3((n + 255) / 256), dim3(256), 0, st, p, value, n);
+    return hipGetLastError();
+}
+
+hipError_t launch_quantise_table(const DevTable &t, hipStream_t st) {
+    hipLaunchKernelGGL(quantise_table_kernel, dim3(t.rows), dim3(256), 0, st, t);
+    return hipGetLastError();
+}
+
+hipError_t launch_build_grid(const DevTable &t, int limit, hipStream_t st) {
+    hipLaunchKernelGGL(build_grid_kernel, dim3(t.rows), dim3(kGridThreads), 0, st, t, limit);
     return hipGetLastError();
 }
 

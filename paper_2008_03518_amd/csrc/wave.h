@@ -35,6 +35,12 @@ __device__ __forceinline__ double dpp_f64(double v) {
     return __longlong_as_double((long long)dpp_u64<CTRL>((uint64_t)__double_as_longlong(v)));
 }
 
+// Lane l (0..3) of every four lanes to all four.
+template <int L>
+__device__ __forceinline__ double dpp_bcast_f64(double v) {
+    return dpp_f64<L | L << 2 | L << 4 | L << 6>(v);
+}
+
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
     const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
