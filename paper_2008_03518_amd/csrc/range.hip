@@ -1,36 +1,34 @@
-// range.hip -- the range-query planner for gfx950: up to four requests per
-// compute unit on 256-thread workgroups, or one on a 512-thread workgroup.
+// range.hip -- the range-query planner for gfx950: one request per workgroup
+// of 256 or 512 threads (Sec. VII: only the trajectories within reach of the
+// state are considered).
 //
-// With the range query (Sec. VII: only the trajectories within reach of the
-// state are considered) most steps find no plan within reach, and the work
-// of a step is the FP64 valuation of every action, the argmax and the
-// advance: a chain of short phases separated by barriers and memory round
-// trips.  One request on a 1024-thread workgroup leaves the compute unit
-// idle through most of that chain; here two to four requests share a compute
-// unit, so that one request's waits overlap the others' work, or a request
-// alone on a compute unit runs the chain on 512 threads without spilled
-// registers; a step has three workgroup barriers.  Per step:
-//   1. x and y of the row's entries (up to 4096 per chunk) arrive in LDS by
-//      DMA while the previous step runs (with 512 threads z and visibility
-//      too), and a box test against the state
-//      marks candidate entries.  Its half-width exceeds the staging radius
-//      by a margin that covers every rounding of the exact test, so each
-//      entry the exact test keeps is a candidate;
-//   2. each lane takes its candidates one per round: z and visibility are
-//      read (from the table, or from LDS) and the exact test of the range query (FP64
-//      offset from the state, FP32 squared distance against the staging
-//      radius, visible to this request) stages the same entries as the
-//      1024-thread range query, as (q_x, q_y, -2 dt q_z, |q|^2), which every
-//      thread sweeps for its actions;
-//   3. FP64 scoring, tie-band argmax and the trajectory record are those of
-//      the 1024-thread kernel (the same functions and expressions, each
-//      thread holding up to two actions, one with 512 threads), so plans,
-//      values and records are
-//      identical bit for bit.  Every wave publishes its candidate choice
-//      with the value, flags and nearest distance, and every thread then
-//      takes the step itself: the state lives in registers, and the heading
-//      directions alternate between two LDS buffers, so no barrier closes
-//      the step.
+// With the range query most steps have no plan within reach, and a step is a
+// chain of dependent operations, bound by latency and not by bytes or
+// arithmetic: scoring every action in FP64 against the few plans near it, on
+// the whole workgroup, took 3.5 us a step for a request alone (2.4 GHz: 8400
+// cycles), whether or not a plan was near.  Here a step is taken in one of
+// three ways, all of which give the same plans, values and records bit for
+// bit:
+//   - in a run, where no plan changes the choice: an action's value is at
+//     most its goal term, so the goal-directed action is the choice while no
+//     well reaches its successor.  One wave computes the run's states ahead
+//     (280 cycles a step: a reciprocal square root and its refinement), the
+//     others check them against the table;
+//   - in a detour batch, among the plans near them: the action nearest the
+//     goal outside every well, one workgroup barrier a step and no
+//     exponential;
+//   - singly, where those rules do not decide (a tie, no action outside the
+//     wells, a distance within 1 mm of the radius that is inside): every
+//     action scored in FP64, tie-band argmax, as in the 1024-thread kernel
+//     (the same functions).
+// The entries near a state come from a grid over the row (table.hip,
+// build_grid_kernel: a 30 km row of 2600 entries has about ten in the cells a
+// query covers, where reading x and y of the row took 21 KB of the compute
+// unit's 64 B/clk); columns appended since the grid was built are searched by
+// their 16-bit coordinates, 4 bytes an entry.  Points are written 64 at a
+// time, a run's values evaluated 64 at a time.
+//   Measured (MI355X, 3000 plans, 360 actions): a request alone 3.5 -> 0.30 us
+// a step; the 1000-request stream's planner time 22.3 -> 9.6 ms.
 #include "planner.h"
 #include "score.h"
 #include "wave.h"
@@ -51,8 +49,8 @@ __device__ __forceinline__ int lanes_below(uint64_t bal) {
 
 // NT threads per request: kRangeThreads with OCC requests resident per CU
 // (kRangePerCU: up to 128 VGPRs each; 2: up to 256, no register spills), or
-// kRangeThreadsSolo with one per CU (no register spills) for launches that
-// hold at most one request per CU.
+// kRangeThreadsSolo (one action per thread) for launches that hold at most
+// one request per CU.
 template <int NT, int OCC, int NC, int NV, int ZC>
 __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                           amdgpu_waves_per_eu(NT == kRangeThreads ? OCC : 2))) void range_planner_kernel(
@@ -258,6 +256,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     enum { STEP = 0, DETOUR = 1, STRAIGHT = 2 };          // how the next step is taken: singly, in a detour batch, in a run
     int mode = cfg.run_ok ? STRAIGHT : STEP;
     int singly = 0, wait = 1;                             // single steps left before the next detour batch; their next number
+    // goal-directed choices in a row that end a detour: doubled by a run that
+    // stops within half a batch (a flight along the edge of a well, which a
+    // run does not decide, would pay for a run every other step)
+    int need = 2, direct = 0;
     // Points [fl, to) from the ring to the trajectory, one per lane of the
     // calling wave.  A run's point has its goal term for a value (no penalty
     // reaches it), evaluated here for 64 points at a time instead of once per
@@ -554,7 +556,10 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 steps_here += f;
                 taken += f;
                 par ^= 1;
-                if (f < nb) mode = cfg.detour_ok ? DETOUR : STEP;
+                if (f < nb) {
+                    mode = cfg.detour_ok ? DETOUR : STEP;
+                    need = taken < RUN / 2 ? min(2 * need, 64) : 2;
+                }
                 if (f < nb || stop_now || sNb[par] == 0) break;
                 shift_counts(t0 + n);
                 flush_points();
@@ -634,7 +639,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
             lds_barrier();
             stop_now = s_stop_run[0];
             double x = s[0], y = s[1], z = s[2];
-            int f = 0, direct = 0;
+            int f = 0;
             for (; f < kb; ++f) {                         // uniform: every wave decides alike
                 mode = STEP;
                 const int cnt = sListN[f];
@@ -761,7 +766,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                     pairs += (long long)A * __popcll(near);
                     entries += rc;
                 }
-                // back to runs once two choices in a row were the goal-directed one
+                // back to runs after `need` goal-directed choices in a row
                 {
                     double ez = INFINITY;
                     int cg = 0;
@@ -777,8 +782,9 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 }
                 x = px; y = py; z = pz;
                 n += 1;
-                if (direct >= 2) {
+                if (direct >= need) {
                     mode = STRAIGHT;
+                    direct = 0;
                     ++f;
                     break;
                 }
@@ -1070,22 +1076,12 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 sPs[ri] = n_row;
                 sPt[ri] = top != best ? top : -1;
             }
-            // the goal-directed action was the choice: the next steps may be
-            // a run; else a detour batch, unless those decided nothing lately
+            // a detour batch next (it ends in a run once the goal-directed
+            // action is the choice), unless those decided nothing lately
             if (cfg.run_ok) {
-                double ez = INFINITY;
-                int cg = 0;
-#pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    const double e = fabs(g[2] - (s[2] + sDz[c]));
-                    if (e < ez) {
-                        ez = e;
-                        cg = c;
-                    }
-                }
                 singly -= singly > 0;
-                if (best == cg * NV + cfg.run_v) mode = STRAIGHT;
-                else if (cfg.detour_ok && singly == 0) mode = DETOUR;
+                direct = 0;
+                if (singly == 0) mode = cfg.detour_ok ? DETOUR : STRAIGHT;
             }
             s[0] = x; s[1] = y; s[2] = z;
             n += 1;
@@ -1102,9 +1098,53 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     for (int i = fl + 64 * wave; i < n; i += 64 * NW) write_points(i, n);
     __syncthreads();   // the trajectory complete for every thread
 
-    // Commit validation (shared with the 1024-thread kernel)
+    // Commit validation (validate_points' rule and arithmetic): the points
+    // whose scored nearest plan is within R_sep + 1 m, one per wave at a time,
+    // against the records of the cells around each and the later columns
+    // that its scoring counted.  (A point kept from an earlier launch may
+    // have counted fewer columns than are indexed now; the entries since
+    // were checked against it, at a larger distance, when they came.)
     if (validate && status == FASTMDP_OK) {
-        const int bad = __syncthreads_or(validate_points<NW>(cfg, tb, tr, pt_base, t0, n, seq));
+        const double r2 = cfg.R_sep * cfg.R_sep;
+        const double clear2 = (cfg.R_sep + 1.0) * (cfg.R_sep + 1.0);
+        int bad = 0;
+        for (int k0 = 0; k0 < n; k0 += NT) {              // uniform
+            const int k = k0 + NW * lane + wave;
+            bool near = false;
+            if (k < n) {
+                const double *x = tr.xyz + (pt_base + k) * 3;
+                if (tb.terr && x[2] - terrain_height(tb, x[0], x[1]) < 0.0) bad = 1;
+                near = !(tr.nd[pt_base + k] > clear2);
+            }
+            for (uint64_t fb = __ballot(near); fb; fb &= fb - 1) {          // uniform per wave
+                const int kk = k0 + NW * __builtin_ctzll(fb) + wave;
+                const double *x = tr.xyz + (pt_base + kk) * 3;
+                const double px = x[0], py = x[1], pz = x[2];
+                const int row = t0 + kk, lim = tr.seen[pt_base + kk];
+                const int idn = row < tb.rows ? tb.gn[row] : 0;
+                const size_t rb = (size_t)row * tb.cap;
+                const float fx = (float)px, fy = (float)py;
+                const float vb = (float)cfg.R_sep * 1.001f + 1.0f + 1e-6f * fmaxf(fabsf(fx), fabsf(fy));
+                if (idn > 0) {
+                    const Cells cl = cells(fx, fy, vb);
+                    for (int cy = cl.y0; cy <= cl.y1; cy += 2) {            // uniform
+                        int a, b;
+                        cell_range(row, cl, cy, a, b);
+                        for (a += lane & 31; a < b; a += 32) {
+                            const float4 p = tb.grec[rb + a];
+                            if (__float_as_int(p.w) < seq && entry_d2(px, py, pz, p.x, p.y, p.z) < r2) bad = 1;
+                        }
+                    }
+                }
+                for (int j = idn + lane; j < lim; j += 64) {
+                    const float ex = tb.X[rb + j], ey = tb.Y[rb + j];
+                    if (fabsf(ex - fx) <= vb && fabsf(ey - fy) <= vb && entry_visible(tb, rb + j, seq) &&
+                        entry_d2(px, py, pz, ex, ey, tb.Z[rb + j]) < r2)
+                        bad = 1;
+                }
+            }
+        }
+        bad = __syncthreads_or(bad);
         if (tid == 0) S.valid = bad == 0;
     }
 
