@@ -251,7 +251,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     };
 
     long long pairs = 0, entries = 0;                     // this thread's share (counted by one thread or one lane per step)
-    int steps_here = 0, stop_v = 0, buf = 0, rpar = 0, dpar = 0;
+    int steps_here = 0, stop_v = 0, buf = 0, dpar = 0;
     bool stop_now = false;
     enum { STEP = 0, DETOUR = 1, STRAIGHT = 2 };          // how the next step is taken: singly, in a detour batch, in a run
     int mode = cfg.run_ok ? STRAIGHT : STEP;
@@ -290,6 +290,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
             if (wave == NW - 1) write_points(fl, fl + 64);
             fl += 64;
         }
+    };
+    // The launch stop counter, by one thread per batch: the value on its way
+    // since an earlier batch, and every fourth time a new read (all workgroups
+    // of a launch read this one word, past their caches)
+    int polls = 0;
+    auto poll_stop = [&](int &flag) {
+        flag = stop.target > 0 && stop_v >= stop.target;
+        if (stop.target > 0 && (polls++ & 3) == 0)
+            stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
     // the state's component of this lane (x, y, z, x of every four lanes)
     const int comp = (lane & 3) == 3 ? 0 : lane & 3;
@@ -479,10 +488,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                         sNg[par][st] = nkeep;
                         sOk[par][st] = (gb >> (4 * st) & 15u) == 15u;
                     }
-                    if (lane == 0 && stop.target > 0) {
-                        stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        s_stop_run[par] = stop_v >= stop.target;
-                    }
+                    if (lane == 0) poll_stop(s_stop_run[par]);
                 } else {
                     for (int st = wave - 2; st < nb; st += NW - 2) {        // uniform per wave
                         const int row = tr0 + st, n_row = row_count(row), idn = row_indexed(row);
@@ -551,7 +557,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                     pairs += (long long)A * nk;
                     entries += cnt;
                 }
-                stop_now = stop.target > 0 && s_stop_run[par];
+                stop_now = s_stop_run[par];
                 n += f;
                 steps_here += f;
                 taken += f;
@@ -582,8 +588,6 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
         //    not decide (no action outside the wells, a tie, terrain within
         //    reach) is left to the single step below.
         if (mode == DETOUR) {                             // uniform
-            if (tid == 0 && stop.target > 0)
-                stop_v = __hip_atomic_load(stop.ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             const int kb = min(DS, min(cfg.max_steps - k, budget - steps_here));
 #pragma unroll
             for (int i = 0; i < DS / NW; ++i) {
@@ -635,7 +639,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 }
                 if (lane == 0) sListN[kk] = cnt;
             }
-            if (tid == 0) s_stop_run[0] = stop.target > 0 && stop_v >= stop.target;
+            if (tid == 0) poll_stop(s_stop_run[0]);
             lds_barrier();
             stop_now = s_stop_run[0];
             double x = s[0], y = s[1], z = s[2];
@@ -669,9 +673,11 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 // infinity inside a well (or out of the box)
                 const double xyz[3] = {x, y, z};
                 double b1 = INFINITY, b2 = INFINITY, bn = INFINITY, qx = x, qy = y, qz = z;
+                double d2q[APT], dnq[APT];
                 int ba = 0;
 #pragma unroll
                 for (int q = 0; q < APT; ++q) {
+                    d2q[q] = dnq[q] = INFINITY;
                     if (wave * 64 + q * NT >= A) continue;                  // uniform per wave
                     const int a = min(tid + q * NT, A - 1), h = a / (NC * NV), c = (a / NV) % NC, v = a % NV;
                     const double dx = dot2(cb, sC0[h], -sb, sS0[h]), dy = dot2(sb, sC0[h], cb, sS0[h]);
@@ -693,6 +699,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                     }
                     const double dn = nearest_d2<NC, NV>(at, a, m);
                     if (tid + q * NT >= A || outside_box(cfg, px, py, pz) || dn <= cfg.band_lo2) d2 = INFINITY;
+                    d2q[q] = d2;
+                    dnq[q] = dn;
                     const bool less = d2 < b1;
                     b2 = fmin(b2, less ? b1 : d2);
                     if (less) {
@@ -735,24 +743,92 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 int close = 0;
 #pragma unroll
                 for (int w = 0; w < NW; ++w) close += w != w1 && sR[dpar][w][0] <= lim;
-                const int best = sRa[dpar][w1];
-                const double px = sR[dpar][w1][1], py = sR[dpar][w1][2], pz = sR[dpar][w1][3];
+                int best = sRa[dpar][w1], top = -1;
+                double px = sR[dpar][w1][1], py = sR[dpar][w1][2], pz = sR[dpar][w1][3];
                 double dn = sR[dpar][w1][4];
-                const bool alone = d1 < INFINITY && close == 0 && sRn[dpar][w1] == 1;
+                const bool alone = close == 0 && sRn[dpar][w1] == 1;
                 dpar ^= 1;
-                if (!alone) break;
-                if (dn < cfg.band_hi2) {
-                    // within kBand of the radius: the nearest distance in
-                    // FP64 over the entries in reach, as the single step has it
-                    double dd = INFINITY;
-                    if (keep) {
-                        const float4 p = sList[f][lane];
-                        dd = entry_d2(px, py, pz, p.x, p.y, p.z);
+                if (!(d1 < INFINITY)) break;              // no action outside the wells
+                if (alone) {
+                    if (dn < cfg.band_hi2) {
+                        // within kBand of the radius: the nearest distance in
+                        // FP64 over the entries in reach, as the single step
+                        // has it
+                        double dd = INFINITY;
+                        if (keep) {
+                            const float4 p = sList[f][lane];
+                            dd = entry_d2(px, py, pz, p.x, p.y, p.z);
+                        }
+                        dn = -wave_max(-dd);
+                        if (!(dn >= cfg.R_intr * cfg.R_intr)) break;
                     }
-                    dn = -wave_max(-dd);
-                    if (!(dn >= cfg.R_intr * cfg.R_intr)) break;
+                    if (tb.terr && !(pz - terrain_height(tb, px, py) >= cfg.R_terr)) break;
+                } else {
+                    // several come as near (the two headings beside a plan on
+                    // the track): their goal terms, then the single step's
+                    // argmax among them
+                    double V[APT], v1 = -INFINITY;
+                    bool bad = false;
+#pragma unroll
+                    for (int q = 0; q < APT; ++q) {
+                        V[q] = -INFINITY;
+                        if (!(d2q[q] <= lim)) continue;
+                        const int a = tid + q * NT, h = a / (NC * NV);
+                        double ux, uy, uz;
+                        successor(cfg, at, a, xyz, dot2(cb, sC0[h], -sb, sS0[h]), dot2(sb, sC0[h], cb, sS0[h]), ux, uy, uz);
+                        V[q] = goal_term(cfg, ux, uy, uz, g);
+                        v1 = fmax(v1, V[q]);
+                        bad = bad || !(dnq[q] >= cfg.band_hi2) ||
+                              (tb.terr && !(uz - terrain_height(tb, ux, uy) >= cfg.R_terr));
+                    }
+                    v1 = wave_max(v1);
+                    const uint64_t undecided = __ballot(bad);
+                    if (lane == 0) {
+                        red_d[wave] = v1;
+                        s_wfl[wave] = undecided != 0;
+                    }
+                    lds_barrier();
+                    double vm = -INFINITY;
+                    bool any_bad = false;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) {
+                        vm = fmax(vm, red_d[w]);
+                        any_bad = any_bad || s_wfl[w];
+                    }
+                    const double thr = vm - cfg.tie_rel * fabs(vm);
+                    int li = 0x7fffffff, ti = 0x7fffffff;
+#pragma unroll
+                    for (int q = APT - 1; q >= 0; --q) {  // lowest index last
+                        if (V[q] > -INFINITY && V[q] >= thr) li = tid + q * NT;
+                        if (V[q] > -INFINITY && V[q] == vm) ti = tid + q * NT;
+                    }
+                    li = wave_min(li);
+                    ti = wave_min(ti);
+                    if (lane == 0) {
+                        s_wli[wave] = li;
+                        s_wti[wave] = ti;
+                    }
+#pragma unroll
+                    for (int q = 0; q < APT; ++q)
+                        if (tid + q * NT == li) s_wd2[wave] = dnq[q];
+                    lds_barrier();
+                    best = top = 0x7fffffff;
+                    int bw = 0;
+#pragma unroll
+                    for (int w = 0; w < NW; ++w) {
+                        if (s_wli[w] < best) {
+                            best = s_wli[w];
+                            bw = w;
+                        }
+                        top = min(top, s_wti[w]);
+                    }
+                    // (the next writes to these follow at least one barrier)
+                    if (any_bad || best == 0x7fffffff) break;
+                    dn = s_wd2[bw];
+                    top = top != best ? top : -1;
+                    const int h = best / (NC * NV);
+                    successor(cfg, at, best, xyz, dot2(cb, sC0[h], -sb, sS0[h]), dot2(sb, sC0[h], cb, sS0[h]), px, py, pz);
                 }
-                if (tb.terr && !(pz - terrain_height(tb, px, py) >= cfg.R_terr)) break;
                 mode = DETOUR;
                 if (tid == 0) {
                     const int ri = n % RING, rc = row_count(t + 1 + f);
@@ -762,7 +838,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                     sPd[ri] = dn;
                     sPa[ri] = best | 1 << 16;
                     sPs[ri] = rc;
-                    sPt[ri] = -1;
+                    sPt[ri] = top;
                     pairs += (long long)A * __popcll(near);
                     entries += rc;
                 }
