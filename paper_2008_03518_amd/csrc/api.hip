@@ -84,43 +84,33 @@ struct fastmdp_ctx {
     void *dScratch = nullptr;             // this device's `scratch` (allocation-free plan loading)
     std::vector<int> hRowTmp;             // row counts being checked by fastmdp_load_plans_noalloc
     Slot *dSlots = nullptr;
-    int *dList = nullptr, *dOrder = nullptr, *dNdone = nullptr;
     Traj tr{};
     double *dEv = nullptr;        // 4*A eval outputs
     int *dBest = nullptr;
     double *dPts = nullptr;       // stride*3 commit staging (FP64 trajectory)
     int *dFlag = nullptr;
-    // FCFS withdrawal log
-    int *dDlRow = nullptr, *dDlCol = nullptr, *dDlEp = nullptr, *dDlLen = nullptr, *dDlStart = nullptr;
-    int *dDlOwn = nullptr;
-    float *dDlX = nullptr, *dDlY = nullptr;
-    // acceptance-pass work buffers (fmdp::PassBufs)
-    int *dRowNPre = nullptr, *dInsList = nullptr, *dInsN = nullptr;
+    DeathLog dl[2]{};                     // FCFS withdrawals: of the last pass and of the one running
+    int *dRowNPre = nullptr, *dInsN = nullptr;   // acceptance-pass work buffers (fmdp::PassBufs)
+    int4 *dIns = nullptr;
     float4 *dBox = nullptr;
-    int dl_cap = 0, dl_start_cap = 0;
     // pinned host mirrors and the trajectory gather buffers of the FCFS engine
     Slot *hSlots = nullptr;
-    int *dList2 = nullptr;
-    long long *dOff = nullptr;
-    void *dGather = nullptr, *hGather = nullptr;
+    void *hGather = nullptr;
     size_t gather_cap = 0;                // bytes
     hipEvent_t e0 = nullptr, e1 = nullptr;
     hipEvent_t eGather = nullptr;         // after the last trajectory gather's copy to the host
     hipStream_t gstream = nullptr;        // the gathers' stream: their copies leave the planning stream free
-    // pinned staging of the engine's small per-round transfers (the copies
-    // read or write it when the stream reaches them, so each region is
-    // rewritten only after the round's synchronisation): gather offsets, the
-    // launch list, the pass list, the gather list, and the withdrawal log's
-    // epoch start and length
+    // pinned lists of the engine's rounds, read by the kernels in place (each
+    // is rewritten only after the round's synchronisation): gather offsets,
+    // the launch list, the pass list and the gather list
     void *hRound = nullptr;
     long long *hOff = nullptr;
-    int *hList = nullptr, *hPass = nullptr, *hList2 = nullptr, *hDl = nullptr;
+    int *hList = nullptr, *hPass = nullptr, *hList2 = nullptr;
     // learned action proposal
     fmdp::PropArgs prop{};
     float *dEvF = nullptr;        // proposal eval outputs: features, logits
     int *dEvI = nullptr;          // top-k, certified, proposal's action
     int *dStop = nullptr;         // finished-workgroup counter of a planner launch
-    int *dPass = nullptr;         // slots of an acceptance pass
     fmdp::BatchState bs{};        // co-simulated batch: peaks and step bookkeeping
     std::mutex mu;
     // counters of the last call
@@ -155,18 +145,19 @@ void free_all(fastmdp_ctx *c) {
     hipFree(c->tb.X); hipFree(c->tb.Y); hipFree(c->tb.Z); hipFree(c->tb.rowN);
     hipFree(c->tb.vis); hipFree(c->tb.own); hipFree(c->tb.dead);
     hipFree(c->tb.Q); hipFree(c->tb.grec); hipFree(c->tb.goff); hipFree(c->tb.gn);
-    hipFree(c->dDlRow); hipFree(c->dDlCol); hipFree(c->dDlEp); hipFree(c->dDlLen); hipFree(c->dDlStart);
-    hipFree(c->dDlOwn); hipFree(c->dDlX); hipFree(c->dDlY);
-    hipFree(c->dRowNPre); hipFree(c->dInsList); hipFree(c->dInsN); hipFree(c->dBox);
+    for (DeathLog &d : c->dl) {
+        hipFree(d.x); hipFree(d.y); hipFree(d.z); hipFree(d.col);
+        hipFree(d.seg); hipFree(d.seg_box); hipFree(d.box); hipFree(d.n);
+    }
+    hipFree(c->dRowNPre); hipFree(c->dIns); hipFree(c->dInsN); hipFree(c->dBox);
     hipFree(c->dTerr);
-    hipFree(c->dSlots); hipFree(c->dList); hipFree(c->dOrder); hipFree(c->dNdone);
+    hipFree(c->dSlots);
     hipFree(c->tr.xyz); hipFree(c->tr.act); hipFree(c->tr.val); hipFree(c->tr.seen); hipFree(c->tr.top);
     hipFree(c->tr.ep); hipFree(c->tr.col); hipFree(c->tr.nd); hipFree(c->tr.seenw);
     hipFree(c->dEv); hipFree(c->dBest); hipFree(c->dPts); hipFree(c->dFlag);
     if (c->hSlots) hipHostFree(c->hSlots);
     if (c->hGather) hipHostFree(c->hGather);
-    hipFree(c->dGather); hipFree(c->dList2); hipFree(c->dOff);
-    hipFree(c->dEvF); hipFree(c->dEvI); hipFree(c->dStop); hipFree(c->dPass);
+    hipFree(c->dEvF); hipFree(c->dEvI); hipFree(c->dStop);
     hipFree(c->bs.pk); hipFree(c->bs.owner); hipFree(c->bs.n); hipFree(c->bs.active); hipFree(c->bs.prev_n);
     hipFree(c->bs.any);
     if (c->e0) hipEventDestroy(c->e0);
@@ -307,7 +298,6 @@ int timed_planner(fastmdp_ctx *c, int nblk, const int *list, int budget, int val
     const int nt = fmdp::kPlanThreads;
     HIP_TRY(hipEventRecord(c->e0, c->stream));
     const fmdp::LaunchStop stop{c->dStop, stop_target};
-    if (stop_target > 0) HIP_TRY(fmdp::launch_fill_int(c->dStop, 0, 1, c->stream));
     hipError_t e = fmdp::launch_planner(nblk, nt, c->stream, c->dc, c->tb, c->dSlots, list, c->tr, budget, validate,
                                         epoch, ev, c->prop, stop, mates);
     if (e != hipSuccess) {
@@ -352,7 +342,6 @@ Slot fresh_slot(const fastmdp_request &r, int req_index, int seq) {
     s.status = fmdp::kRunning;
     s.req = req_index;
     s.resume_at = -1;
-    s.clean_ep = -1;
     return s;
 }
 
@@ -371,11 +360,9 @@ int copy_plan_out(fastmdp_ctx *c, int slot, const Slot &s, fastmdp_plan *out) {
     return 0;
 }
 
-// Copy the trajectories of accepted slots to the callers' plans: one gather
-// kernel into a device staging buffer, one copy into pinned host memory.
 // Accepted trajectories on their way to the caller's plans: the device
-// packs them into one buffer and copies it to pinned host memory; the host
-// unpacks after a later synchronisation.
+// packs them into one pinned host buffer; the host unpacks after a later
+// synchronisation.
 struct PendingPlans {
     std::vector<int> slots, reqs, n, status, t0;
     std::vector<long long> off;
@@ -402,12 +389,10 @@ int gather_enqueue(fastmdp_ctx *c, const std::vector<int> &slots, const std::vec
     const size_t bytes = (size_t)pp.total * (3 * sizeof(double) + sizeof(double) + sizeof(int));
     if (bytes > c->gather_cap) {            // no copy is in flight here: the last one was unpacked
         const size_t cap = std::max(bytes, 2 * c->gather_cap);
-        hipFree(c->dGather);
         if (c->hGather) hipHostFree(c->hGather);
-        c->dGather = c->hGather = nullptr;
+        c->hGather = nullptr;
         c->gather_cap = 0;
-        if (hipMalloc(&c->dGather, cap) != hipSuccess || hipHostMalloc(&c->hGather, cap) != hipSuccess)
-            return FASTMDP_E_NOMEM;
+        if (hipHostMalloc(&c->hGather, cap) != hipSuccess) return FASTMDP_E_NOMEM;
         c->gather_cap = cap;
     }
     if (m > c->max_slots) return FASTMDP_E_CAPACITY;
@@ -416,10 +401,7 @@ int gather_enqueue(fastmdp_ctx *c, const std::vector<int> &slots, const std::vec
     // on the gathers' own stream, so that the planning stream's next launch
     // does not wait for the copy; the caller has synchronised the planning
     // stream, and nothing it runs before these slots are reused writes them
-    HIP_TRY(hipMemcpyAsync(c->dList2, c->hList2, m * sizeof(int), hipMemcpyHostToDevice, c->gstream));
-    HIP_TRY(hipMemcpyAsync(c->dOff, c->hOff, m * sizeof(long long), hipMemcpyHostToDevice, c->gstream));
-    HIP_TRY(fmdp::launch_gather_traj(c->dSlots, c->dList2, m, c->dOff, pp.total, c->tr, c->dGather, c->gstream));
-    HIP_TRY(hipMemcpyAsync(c->hGather, c->dGather, bytes, hipMemcpyDeviceToHost, c->gstream));
+    HIP_TRY(fmdp::launch_gather_traj(c->dSlots, c->hList2, m, c->hOff, pp.total, c->tr, c->hGather, c->gstream));
     HIP_TRY(hipEventRecord(c->eGather, c->gstream));
     return 0;
 }
@@ -486,9 +468,6 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     }
     rc = rc ? rc : dev_alloc(&c->tb.rowN, (size_t)cfg->max_rows);
     rc = rc ? rc : dev_alloc(&c->dSlots, (size_t)c->max_slots);
-    rc = rc ? rc : dev_alloc(&c->dList, (size_t)c->max_slots);
-    rc = rc ? rc : dev_alloc(&c->dOrder, (size_t)c->max_slots);
-    rc = rc ? rc : dev_alloc(&c->dNdone, (size_t)1);
     rc = rc ? rc : dev_alloc(&c->tr.xyz, ssz * 3);
     rc = rc ? rc : dev_alloc(&c->tr.act, ssz);
     rc = rc ? rc : dev_alloc(&c->tr.val, ssz);
@@ -498,30 +477,31 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     rc = rc ? rc : dev_alloc(&c->tr.col, ssz);
     rc = rc ? rc : dev_alloc(&c->tr.nd, ssz);
     if (c->dc.lookahead > 1) rc = rc ? rc : dev_alloc(&c->tr.seenw, ssz * c->dc.lookahead);
-    c->dl_cap = 1 << 22;
-    c->dl_start_cap = 1 << 20;             // one epoch per acceptance round
-    rc = rc ? rc : dev_alloc(&c->dDlRow, (size_t)c->dl_cap);
-    rc = rc ? rc : dev_alloc(&c->dDlCol, (size_t)c->dl_cap);
-    rc = rc ? rc : dev_alloc(&c->dDlEp, (size_t)c->dl_cap);
-    rc = rc ? rc : dev_alloc(&c->dDlOwn, (size_t)c->dl_cap);
-    rc = rc ? rc : dev_alloc(&c->dDlX, (size_t)c->dl_cap);
-    rc = rc ? rc : dev_alloc(&c->dDlY, (size_t)c->dl_cap);
+    for (DeathLog &d : c->dl) {            // a slot withdraws one piece a pass
+        d.cap = (int)std::min<size_t>(ssz, (size_t)1 << 22);
+        d.seg_cap = c->max_slots;
+        d.box_cap = (int)std::min<size_t>((size_t)c->max_slots * fmdp::kRowBlocks,
+                                          (size_t)d.cap / fmdp::kRowBlock + 2 * (size_t)c->max_slots);
+        rc = rc ? rc : dev_alloc(&d.x, (size_t)d.cap);
+        rc = rc ? rc : dev_alloc(&d.y, (size_t)d.cap);
+        rc = rc ? rc : dev_alloc(&d.z, (size_t)d.cap);
+        rc = rc ? rc : dev_alloc(&d.col, (size_t)d.cap);
+        rc = rc ? rc : dev_alloc(&d.seg, (size_t)d.seg_cap);
+        rc = rc ? rc : dev_alloc(&d.seg_box, (size_t)d.seg_cap);
+        rc = rc ? rc : dev_alloc(&d.box, (size_t)d.box_cap);
+        rc = rc ? rc : dev_alloc(&d.n, (size_t)3);
+    }
     rc = rc ? rc : dev_alloc(&c->dRowNPre, (size_t)cfg->max_rows);
-    rc = rc ? rc : dev_alloc(&c->dInsList, (size_t)c->max_slots);
+    rc = rc ? rc : dev_alloc(&c->dIns, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->dInsN, (size_t)1);
     rc = rc ? rc : dev_alloc(&c->dBox, (size_t)c->max_slots * fmdp::kRowBlocks);
-    rc = rc ? rc : dev_alloc(&c->dDlLen, (size_t)1);
-    rc = rc ? rc : dev_alloc(&c->dDlStart, (size_t)c->dl_start_cap);
     rc = rc ? rc : dev_alloc(&c->dEv, (size_t)4 * c->A);
     rc = rc ? rc : dev_alloc(&c->dBest, (size_t)1);
     rc = rc ? rc : dev_alloc(&c->dPts, (size_t)c->stride * 3);
     rc = rc ? rc : dev_alloc(&c->dFlag, (size_t)1);
-    rc = rc ? rc : dev_alloc(&c->dList2, (size_t)c->max_slots);
-    rc = rc ? rc : dev_alloc(&c->dOff, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->dEvF, (size_t)FASTMDP_N_FEAT + fmdp::kMaxActions);
     rc = rc ? rc : dev_alloc(&c->dEvI, (size_t)FASTMDP_MAX_TOPK + 2);
     rc = rc ? rc : dev_alloc(&c->dStop, (size_t)1);
-    rc = rc ? rc : dev_alloc(&c->dPass, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->bs.pk, (size_t)fmdp::kMaxBatch * fmdp::kMatePeaks * 4);
     rc = rc ? rc : dev_alloc(&c->bs.owner, (size_t)fmdp::kMaxBatch * fmdp::kMatePeaks);
     rc = rc ? rc : dev_alloc(&c->bs.n, (size_t)1);
@@ -537,14 +517,13 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     if (!rc && hipEventCreateWithFlags(&c->eGather, hipEventDisableTiming) != hipSuccess) rc = FASTMDP_E_DEVICE;
     if (!rc) {
         const size_t ms = (size_t)c->max_slots;
-        if (hipHostMalloc(&c->hRound, ms * sizeof(long long) + (4 * ms + 2) * sizeof(int)) != hipSuccess) {
+        if (hipHostMalloc(&c->hRound, ms * sizeof(long long) + 3 * ms * sizeof(int)) != hipSuccess) {
             rc = FASTMDP_E_NOMEM;
         } else {
             c->hOff = static_cast<long long *>(c->hRound);
             c->hList = reinterpret_cast<int *>(c->hOff + ms);
             c->hPass = c->hList + ms;
             c->hList2 = c->hPass + ms;
-            c->hDl = c->hList2 + ms;
         }
     }
     if (rc) {
@@ -906,13 +885,9 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
     std::vector<int> list, pass;
     PendingPlans pending;                    // accepted trajectories still being copied
     bool gathered = false;                   // a gather was enqueued in this call
-    // withdrawal log of this call: epoch e's withdrawals start at dl_start[e]
-    int epoch = 0, dl_len = 0;
-    std::vector<int> dl_start(2, 0);
-    HIP_TRY(fmdp::launch_fill_int(ctx->dDlLen, 0, 1, ctx->stream));
-    HIP_TRY(fmdp::launch_fill_int(ctx->dDlStart, 0, 2, ctx->stream));
-    DeathLog dl{ctx->dDlRow, ctx->dDlCol, ctx->dDlEp, ctx->dDlLen, ctx->dl_cap, ctx->dDlStart,
-                ctx->dDlX, ctx->dDlY, ctx->dDlOwn};
+    int epoch = 0;                           // acceptance passes run
+    const fmdp::PassBufs pbufs{ctx->dRowNPre, ctx->dIns, ctx->dInsN, ctx->dBox, ctx->dStop, ctx->hSlots};
+    HIP_TRY(fmdp::launch_fcfs_begin(ctx->tb, pbufs, ctx->dl[0], ctx->dl[1], ctx->stream));
     auto finish = [&](int rc) {
         // the device row counts include tentative and withdrawn entries
         if (hipMemcpyAsync(ctx->hRowN.data(), ctx->tb.rowN, ctx->hRowN.size() * sizeof(int), hipMemcpyDeviceToHost,
@@ -968,16 +943,14 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 if (wait > 0) std::this_thread::sleep_for(std::chrono::duration<double>(std::min(wait, 0.001)));
                 continue;
             }
-            // One synchronisation per round: the planner launch, the acceptance
-            // pass over every admitted, not yet accepted request (its kernels
-            // skip the ones still planning), the copy of the slots back, and the
-            // trajectories accepted in the previous round on their way to the
-            // caller's plans, all in stream order.
+            // One synchronisation per round: the planner launch and the
+            // acceptance pass over every admitted, not yet accepted request,
+            // in stream order, the slots written to the host's mirror by the
+            // pass itself; the trajectories accepted in the previous round
+            // reach the caller's plans meanwhile.
             const bool planned = !list.empty();
             if (planned) {
                 std::memcpy(ctx->hList, list.data(), list.size() * sizeof(int));
-                HIP_TRY(hipMemcpyAsync(ctx->dList, ctx->hList, list.size() * sizeof(int), hipMemcpyHostToDevice,
-                                       ctx->stream));
                 EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
                 // the launch ends once a quarter of its requests have finished:
                 // the others resume after the acceptance pass, with new requests
@@ -989,25 +962,15 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 // half)
                 const int stop_div = fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ? 2 : 4;
                 const int stop_target = std::max(1, (int)list.size() / stop_div);
-                int rc = timed_planner(ctx, (int)list.size(), ctx->dList, budget, 1, epoch, none, stop_target, false);
+                int rc = timed_planner(ctx, (int)list.size(), ctx->hList, budget, 1, epoch, none, stop_target, false);
                 if (rc) return finish(rc);
             }
             pass.clear();
             for (int r = next_commit; r < next_req; ++r) pass.push_back(req_slot[r]);
             epoch += 1;
-            if (epoch + 1 >= ctx->dl_start_cap) return finish(FASTMDP_E_CAPACITY);
-            dl_start.resize(epoch + 1);
-            dl_start[epoch] = dl_len;
-            ctx->hDl[0] = dl_len;
             std::memcpy(ctx->hPass, pass.data(), pass.size() * sizeof(int));
-            HIP_TRY(hipMemcpyAsync(ctx->dDlStart + epoch, ctx->hDl, sizeof(int), hipMemcpyHostToDevice, ctx->stream));
-            HIP_TRY(hipMemcpyAsync(ctx->dPass, ctx->hPass, pass.size() * sizeof(int), hipMemcpyHostToDevice,
-                                   ctx->stream));
-            const fmdp::PassBufs pbufs{ctx->dRowNPre, ctx->dInsList, ctx->dInsN, ctx->dBox};
-            HIP_TRY(fmdp::launch_fcfs_pass(ctx->dc, ctx->tb, ctx->dSlots, ctx->dPass, (int)pass.size(), ctx->tr, dl,
-                                           pbufs, epoch, dl_len, ctx->stream));
-            HIP_TRY(hipMemcpyAsync(hs, ctx->dSlots, S * sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
-            HIP_TRY(hipMemcpyAsync(ctx->hDl + 1, ctx->dDlLen, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+            HIP_TRY(fmdp::launch_fcfs_pass(ctx->dc, ctx->tb, ctx->dSlots, ctx->hPass, (int)pass.size(), ctx->tr,
+                                           ctx->dl[(epoch - 1) & 1], ctx->dl[epoch & 1], pbufs, epoch, ctx->stream));
             // the trajectories accepted last round were gathered ahead of this
             // round's launch: hand them to the caller while the planner runs
             if (!pending.empty()) {
@@ -1015,12 +978,10 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 gather_unpack(ctx, pending, plans);
             }
             HIP_TRY(hipStreamSynchronize(ctx->stream));
-            dl_len = ctx->hDl[1];
             if (planned) {
                 int rc = planner_time(ctx);
                 if (rc) return finish(rc);
             }
-            if (dl_len > ctx->dl_cap) return finish(FASTMDP_E_CAPACITY);
             for (int s : pass) {
                 if (hs[s].err) return finish(FASTMDP_E_CAPACITY);
             }
@@ -1076,8 +1037,8 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
     int m = 0;
     for (int s = 0; s < S; ++s)
         if (slot_req[s] >= 0) ctx->hPass[m++] = s;
-    if (m > 0 && hipMemcpyAsync(ctx->dPass, ctx->hPass, m * sizeof(int), hipMemcpyHostToDevice, ctx->stream) == hipSuccess)
-        fmdp::launch_fcfs_abort(ctx->tb, ctx->dSlots, ctx->dPass, m, ctx->tr, seq0 + next_commit, epoch + 1,
+    if (m > 0)
+        fmdp::launch_fcfs_abort(ctx->tb, ctx->dSlots, ctx->hPass, m, ctx->tr, seq0 + next_commit, epoch + 1,
                                 ctx->stream);
     for (int r = next_commit; r < n; ++r) committed[r] = 0;
     ctx->seq = seq0 + next_commit;

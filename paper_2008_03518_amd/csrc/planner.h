@@ -118,8 +118,6 @@ struct Slot {
     int cert_miss;    // proposal steps that fell back to the full sweep, accumulated
     int first;        // FCFS check: first affected point found so far (INT_MAX if none)
     int resumes;      // FCFS: times the request went back to planning, accumulated
-    int clean_ep;     // FCFS: the pass whose check found the whole trajectory consistent (-1: none since
-                      // it last finished planning)
 };
 
 // Per-slot trajectory buffers, `stride` points per slot.  seen[k] is the
@@ -145,27 +143,36 @@ struct Traj {
     int stride;
 };
 
-// Log of withdrawn table entries (row, column, epoch), in epoch order.
+// Withdrawals of one acceptance pass: every withdrawn piece of a trajectory
+// is a segment (first entry, entries, first row, owner) of consecutive rows,
+// its entries' column and stored position at first entry + row - first row,
+// and its bounding boxes per block of kRowBlock rows (FP32 x min, x max, y
+// min, y max) from box seg_box[i] on.
 struct DeathLog {
-    int *row, *col, *ep;
-    int *len;          // device counter
-    int cap;
-    const int *start;  // start[e]: log length when epoch e's withdrawals began
-    float *x, *y;      // the withdrawn entry's stored x, y
-    int *own;          // and its owner (sequence number)
+    float *x, *y, *z;
+    int *col;
+    int4 *seg;
+    int *seg_box;
+    float4 *box;
+    int *n;            // entries, segments, boxes in use
+    int cap, seg_cap, box_cap;
 };
 
 // Work buffers of the FCFS acceptance pass: the row counts before the
-// pass's insertions, the slots whose trajectories entered entries in it, and
-// per slot the bounding box (FP32 x min, x max, y min, y max) of its points
-// in each block of kRowBlock rows, from the block of its first row on.
+// pass's insertions, the trajectories that entered entries in it (slot,
+// first row, points, sequence number), and per slot the bounding box (as
+// above) of its points in each block of kRowBlock rows, from the block of
+// its first row on; the launch stop counter, cleared for the next launch;
+// the host's mirror of the slots (pinned memory).
 constexpr int kRowBlock = 64;
 constexpr int kRowBlocks = kMaxPoints / kRowBlock + 1;   // row blocks a trajectory can touch
 struct PassBufs {
     int *rowN_pre;     // [rows]
-    int *ins_list;     // [max_slots]
+    int4 *ins;         // [max_slots]
     int *ins_n;        // [1]
     float4 *box;       // [max_slots * kRowBlocks]
+    int *stop;         // [1]
+    Slot *mirror;      // [max_slots]
 };
 
 // Outputs of a single evaluated step (all device pointers, any may be null).
@@ -323,13 +330,19 @@ hipError_t launch_commit_check(const DevCfg &c, const DevTable &t, const double 
 hipError_t launch_commit_append(const DevTable &t, const double *pts, int t0, int n, int own, const int *flag,
                                 hipStream_t st);
 // Pack listed slots' trajectories (points from off[i]) into dst: total*3
-// doubles xyz, total doubles value, total ints action.
+// doubles xyz, total doubles value, total ints action.  list, off and dst may
+// be pinned host memory.
 hipError_t launch_gather_traj(const Slot *slots, const int *list, int n_list, const long long *off, long long total,
                               const Traj &tr, void *dst, hipStream_t st);
-// FCFS pass over the finished, not yet accepted slots in `list`:
-// tentative insert, interaction check, withdrawal (see table.hip).
+// FCFS acceptance: launch_fcfs_begin once before a call's first planner
+// launch (empty logs, row counts as they stand), then after each launch a
+// pass over the admitted, not yet accepted slots in `list` (may be pinned host
+// memory): tentative insert, interaction check, withdrawal (see table.hip).
+// prev and cur are the logs of the pass before and of this one.
+hipError_t launch_fcfs_begin(const DevTable &t, const PassBufs &pb, const DeathLog &a, const DeathLog &b,
+                             hipStream_t st);
 hipError_t launch_fcfs_pass(const DevCfg &c, const DevTable &t, Slot *slots, const int *list, int n_list,
-                            const Traj &tr, const DeathLog &dl, const PassBufs &pb, int epoch, int dl_len,
+                            const Traj &tr, const DeathLog &prev, const DeathLog &cur, const PassBufs &pb, int epoch,
                             hipStream_t st);
 // Withdraw every table entry of the listed slots owned by sequence numbers
 // from min_own on (an interrupted FCFS call).
