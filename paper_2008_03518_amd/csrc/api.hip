@@ -85,10 +85,13 @@ struct fastmdp_ctx {
     std::vector<int> hRowTmp;             // row counts being checked by fastmdp_load_plans_noalloc
     Slot *dSlots = nullptr;
     Traj tr{};
-    double *dEv = nullptr;        // 4*A eval outputs
-    int *dBest = nullptr;
-    double *dPts = nullptr;       // stride*3 commit staging (FP64 trajectory)
-    int *dFlag = nullptr;
+    // pinned host memory of the calls for one state or plan, which the
+    // kernels read and write in place: eval outputs (4 * A), a trajectory to
+    // commit (stride * 3), and hInt = {best action, commit result, aircraft of
+    // a batch still flying}
+    double *hIo = nullptr, *hPts = nullptr;
+    int *hInt = nullptr;
+    int *dFlag = nullptr;         // commit check: per point
     DeathLog dl[2]{};                     // FCFS withdrawals: of the last pass and of the one running
     int *dRowNPre = nullptr, *dInsN = nullptr;   // acceptance-pass work buffers (fmdp::PassBufs)
     int4 *dIns = nullptr;
@@ -154,12 +157,13 @@ void free_all(fastmdp_ctx *c) {
     hipFree(c->dSlots);
     hipFree(c->tr.xyz); hipFree(c->tr.act); hipFree(c->tr.val); hipFree(c->tr.seen); hipFree(c->tr.top);
     hipFree(c->tr.ep); hipFree(c->tr.col); hipFree(c->tr.nd); hipFree(c->tr.seenw);
-    hipFree(c->dEv); hipFree(c->dBest); hipFree(c->dPts); hipFree(c->dFlag);
+    hipFree(c->dFlag);
+    if (c->hIo) hipHostFree(c->hIo);
     if (c->hSlots) hipHostFree(c->hSlots);
     if (c->hGather) hipHostFree(c->hGather);
     hipFree(c->dEvF); hipFree(c->dEvI); hipFree(c->dStop);
     hipFree(c->bs.pk); hipFree(c->bs.owner); hipFree(c->bs.n); hipFree(c->bs.active); hipFree(c->bs.prev_n);
-    hipFree(c->bs.any);
+    
     if (c->e0) hipEventDestroy(c->e0);
     if (c->e1) hipEventDestroy(c->e1);
     if (c->eGather) hipEventDestroy(c->eGather);
@@ -293,13 +297,12 @@ int planner_time(fastmdp_ctx *c) {
 }
 
 int timed_planner(fastmdp_ctx *c, int nblk, const int *list, int budget, int validate, int epoch,
-                  const EvalOut &ev, int stop_target = 0, bool sync = true,
-                  const fmdp::MatePeaks &mates = fmdp::MatePeaks{}) {
+                  const EvalOut &ev, Slot *slots, int stop_target = 0, bool sync = true) {
     const int nt = fmdp::kPlanThreads;
     HIP_TRY(hipEventRecord(c->e0, c->stream));
     const fmdp::LaunchStop stop{c->dStop, stop_target};
-    hipError_t e = fmdp::launch_planner(nblk, nt, c->stream, c->dc, c->tb, c->dSlots, list, c->tr, budget, validate,
-                                        epoch, ev, c->prop, stop, mates);
+    hipError_t e = fmdp::launch_planner(nblk, nt, c->stream, c->dc, c->tb, slots, list, c->tr, budget, validate,
+                                        epoch, ev, c->prop, stop, fmdp::MatePeaks{});
     if (e != hipSuccess) {
         std::fprintf(stderr, "libfastmdp: planner launch failed: %s\n", hipGetErrorString(e));
         return FASTMDP_E_DEVICE;
@@ -345,21 +348,6 @@ Slot fresh_slot(const fastmdp_request &r, int req_index, int seq) {
     return s;
 }
 
-int copy_plan_out(fastmdp_ctx *c, int slot, const Slot &s, fastmdp_plan *out) {
-    const int n = s.n_points;
-    if (out->capacity < n || !out->xyz || !out->action || !out->value) return FASTMDP_E_CAPACITY;
-    const size_t base = (size_t)slot * c->stride;
-    HIP_TRY(hipMemcpyAsync(out->xyz, c->tr.xyz + base * 3, (size_t)n * 3 * sizeof(double), hipMemcpyDeviceToHost,
-                           c->stream));
-    HIP_TRY(hipMemcpyAsync(out->action, c->tr.act + base, (size_t)n * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipMemcpyAsync(out->value, c->tr.val + base, (size_t)n * sizeof(double), hipMemcpyDeviceToHost,
-                           c->stream));
-    out->status = s.status;
-    out->t0 = s.t0;
-    out->n_points = n;
-    return 0;
-}
-
 // Accepted trajectories on their way to the caller's plans: the device
 // packs them into one pinned host buffer; the host unpacks after a later
 // synchronisation.
@@ -370,7 +358,21 @@ struct PendingPlans {
     bool empty() const { return reqs.empty(); }
 };
 
-int gather_enqueue(fastmdp_ctx *c, const std::vector<int> &slots, const std::vector<int> &reqs, const Slot *hs,
+constexpr size_t kPointBytes = 4 * sizeof(double) + sizeof(int);      // a gathered point
+
+// The pinned gather buffer, grown to `bytes` (no copy into it is in flight).
+int gather_reserve(fastmdp_ctx *c, size_t bytes) {
+    if (bytes <= c->gather_cap) return 0;
+    const size_t cap = std::max(bytes, 2 * c->gather_cap);
+    if (c->hGather) hipHostFree(c->hGather);
+    c->hGather = nullptr;
+    c->gather_cap = 0;
+    if (hipHostMalloc(&c->hGather, cap) != hipSuccess) return FASTMDP_E_NOMEM;
+    c->gather_cap = cap;
+    return 0;
+}
+
+int gather_enqueue(fastmdp_ctx *c, const Slot *dslots, const std::vector<int> &slots, const std::vector<int> &reqs, const Slot *hs,
                    const fastmdp_plan *plans, PendingPlans &pp) {
     const int m = (int)slots.size();
     pp = PendingPlans();
@@ -386,22 +388,15 @@ int gather_enqueue(fastmdp_ctx *c, const std::vector<int> &slots, const std::vec
         pp.status.push_back(s.status);
         pp.t0.push_back(s.t0);
     }
-    const size_t bytes = (size_t)pp.total * (3 * sizeof(double) + sizeof(double) + sizeof(int));
-    if (bytes > c->gather_cap) {            // no copy is in flight here: the last one was unpacked
-        const size_t cap = std::max(bytes, 2 * c->gather_cap);
-        if (c->hGather) hipHostFree(c->hGather);
-        c->hGather = nullptr;
-        c->gather_cap = 0;
-        if (hipHostMalloc(&c->hGather, cap) != hipSuccess) return FASTMDP_E_NOMEM;
-        c->gather_cap = cap;
-    }
+    const int grown = gather_reserve(c, (size_t)pp.total * kPointBytes);
+    if (grown) return grown;
     if (m > c->max_slots) return FASTMDP_E_CAPACITY;
     std::memcpy(c->hList2, pp.slots.data(), m * sizeof(int));
     std::memcpy(c->hOff, pp.off.data(), m * sizeof(long long));
     // on the gathers' own stream, so that the planning stream's next launch
     // does not wait for the copy; the caller has synchronised the planning
     // stream, and nothing it runs before these slots are reused writes them
-    HIP_TRY(fmdp::launch_gather_traj(c->dSlots, c->hList2, m, c->hOff, pp.total, c->tr, c->hGather, c->gstream));
+    HIP_TRY(fmdp::launch_gather_traj(dslots, c->hList2, m, c->hOff, pp.total, c->tr, c->hGather, c->gstream));
     HIP_TRY(hipEventRecord(c->eGather, c->gstream));
     return 0;
 }
@@ -422,6 +417,52 @@ void gather_unpack(fastmdp_ctx *c, PendingPlans &pp, fastmdp_plan *plans) {
         p.n_points = n;
     }
     pp = PendingPlans();
+}
+
+// The trajectories of slots 0..n-1 to the caller's plans, for the calls that
+// plan them in one go: enqueued behind the planner, before their lengths are
+// known, each in a place of a whole trajectory's size -- one synchronisation,
+// where three copies to pageable memory per plan took 45 us each call.  Many
+// or long ones (above kDirectBytes) are packed once their lengths are known.
+constexpr size_t kDirectBytes = (size_t)8 << 20;
+
+bool direct_out(const fastmdp_ctx *c, int n) { return (size_t)n * c->stride * kPointBytes <= kDirectBytes; }
+
+int plans_enqueue(fastmdp_ctx *c, const Slot *slots, int n) {
+    if (!direct_out(c, n)) return 0;
+    const long long total = (long long)n * c->stride;
+    const int rc = gather_reserve(c, (size_t)total * kPointBytes);
+    if (rc) return rc;
+    for (int i = 0; i < n; ++i) {
+        c->hList2[i] = i;
+        c->hOff[i] = (long long)i * c->stride;
+    }
+    HIP_TRY(fmdp::launch_gather_traj(slots, c->hList2, n, c->hOff, total, c->tr, c->hGather, c->stream));
+    return 0;
+}
+
+// After the synchronisation that follows plans_enqueue; hs: the slots as the
+// planner left them.
+int plans_collect(fastmdp_ctx *c, const Slot *slots, const Slot *hs, int n, fastmdp_plan *plans) {
+    PendingPlans pp;
+    if (direct_out(c, n)) {
+        pp.total = (long long)n * c->stride;
+        for (int i = 0; i < n; ++i) {
+            pp.reqs.push_back(i);
+            pp.off.push_back((long long)i * c->stride);
+            pp.n.push_back(hs[i].n_points);
+            pp.status.push_back(hs[i].status);
+            pp.t0.push_back(hs[i].t0);
+        }
+    } else {
+        std::vector<int> all(n);
+        for (int i = 0; i < n; ++i) all[i] = i;
+        const int rc = gather_enqueue(c, slots, all, all, hs, plans, pp);
+        if (rc) return rc;
+        HIP_TRY(hipStreamSynchronize(c->gstream));
+    }
+    gather_unpack(c, pp, plans);
+    return 0;
 }
 
 }  // namespace
@@ -495,10 +536,7 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     rc = rc ? rc : dev_alloc(&c->dIns, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->dInsN, (size_t)1);
     rc = rc ? rc : dev_alloc(&c->dBox, (size_t)c->max_slots * fmdp::kRowBlocks);
-    rc = rc ? rc : dev_alloc(&c->dEv, (size_t)4 * c->A);
-    rc = rc ? rc : dev_alloc(&c->dBest, (size_t)1);
-    rc = rc ? rc : dev_alloc(&c->dPts, (size_t)c->stride * 3);
-    rc = rc ? rc : dev_alloc(&c->dFlag, (size_t)1);
+    rc = rc ? rc : dev_alloc(&c->dFlag, (size_t)c->stride);
     rc = rc ? rc : dev_alloc(&c->dEvF, (size_t)FASTMDP_N_FEAT + fmdp::kMaxActions);
     rc = rc ? rc : dev_alloc(&c->dEvI, (size_t)FASTMDP_MAX_TOPK + 2);
     rc = rc ? rc : dev_alloc(&c->dStop, (size_t)1);
@@ -507,9 +545,19 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     rc = rc ? rc : dev_alloc(&c->bs.n, (size_t)1);
     rc = rc ? rc : dev_alloc(&c->bs.active, (size_t)fmdp::kMaxBatch);
     rc = rc ? rc : dev_alloc(&c->bs.prev_n, (size_t)fmdp::kMaxBatch);
-    rc = rc ? rc : dev_alloc(&c->bs.any, (size_t)1);
     if (!rc && hipHostMalloc(reinterpret_cast<void **>(&c->hSlots), (size_t)c->max_slots * sizeof(Slot)) != hipSuccess)
         rc = FASTMDP_E_NOMEM;
+    if (!rc) {
+        const size_t d = (size_t)4 * c->A + (size_t)c->stride * 3;
+        if (hipHostMalloc(reinterpret_cast<void **>(&c->hIo), d * sizeof(double) + 3 * sizeof(int)) != hipSuccess) {
+            rc = FASTMDP_E_NOMEM;
+        } else {
+            c->hPts = c->hIo + (size_t)4 * c->A;
+            c->hInt = reinterpret_cast<int *>(c->hIo + d);
+            c->bs.any = c->hInt + 2;
+        }
+    }
+    rc = rc ? rc : gather_reserve(c, (size_t)c->stride * kPointBytes);
     if (!rc && hipStreamCreate(&c->own) != hipSuccess) rc = FASTMDP_E_DEVICE;
     if (!rc && hipStreamCreate(&c->gstream) != hipSuccess) rc = FASTMDP_E_DEVICE;
     if (!rc && hipEventCreate(&c->e0) != hipSuccess) rc = FASTMDP_E_DEVICE;
@@ -686,23 +734,18 @@ int fastmdp_eval_step(fastmdp_ctx *ctx, const fastmdp_state *state, double *valu
     r.origin = state->pos;
     r.goal = state->goal;
     r.t0 = state->t;
-    Slot s = fresh_slot(r, 0, ctx->seq);
-    HIP_TRY(hipMemcpyAsync(ctx->dSlots, &s, sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
+    Slot &s = ctx->hSlots[0];                          // the kernel reads and writes it in place
+    s = fresh_slot(r, 0, ctx->seq);
     const int A = ctx->A;
-    EvalOut ev{ctx->dEv, ctx->dEv + A, ctx->dEv + 2 * A, ctx->dEv + 3 * A, ctx->dBest};
-    int rc = timed_planner(ctx, 1, nullptr, 1, 0, 0, ev);
+    double *h = ctx->hIo;
+    EvalOut ev{h, h + A, h + 2 * A, h + 3 * A, ctx->hInt};
+    int rc = timed_planner(ctx, 1, nullptr, 1, 0, 0, ev, ctx->hSlots);
     if (rc) return rc;
-    std::vector<double> h(4 * (size_t)A);
-    int b = -1;
-    HIP_TRY(hipMemcpyAsync(h.data(), ctx->dEv, h.size() * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(&b, ctx->dBest, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipMemcpyAsync(&s, ctx->dSlots, sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    if (values) std::memcpy(values, h.data(), A * sizeof(double));
-    if (goal_term) std::memcpy(goal_term, h.data() + A, A * sizeof(double));
-    if (intr_term) std::memcpy(intr_term, h.data() + 2 * A, A * sizeof(double));
-    if (terr_term) std::memcpy(terr_term, h.data() + 3 * A, A * sizeof(double));
-    if (best) *best = b;
+    if (values) std::memcpy(values, h, A * sizeof(double));
+    if (goal_term) std::memcpy(goal_term, h + A, A * sizeof(double));
+    if (intr_term) std::memcpy(intr_term, h + 2 * A, A * sizeof(double));
+    if (terr_term) std::memcpy(terr_term, h + 3 * A, A * sizeof(double));
+    if (best) *best = ctx->hInt[0];
     ctx->st_pairs = s.pairs;
     ctx->st_entries = s.entries;
     ctx->st_steps = s.steps;
@@ -714,18 +757,18 @@ int fastmdp_plan_request(fastmdp_ctx *ctx, const fastmdp_request *req, fastmdp_p
     if (out->capacity < ctx->stride || !out->xyz || !out->action || !out->value) return FASTMDP_E_CAPACITY;
     std::lock_guard<std::mutex> lk(ctx->mu);
     reset_stats(ctx);
-    Slot s = fresh_slot(*req, 0, ctx->seq);
+    Slot &s = ctx->hSlots[0];                          // the kernel reads and writes it in place
+    s = fresh_slot(*req, 0, ctx->seq);
     int rc = refresh_grid(ctx, ctx->seq, false);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(ctx->dSlots, &s, sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
-    rc = timed_planner(ctx, 1, nullptr, ctx->cfg.max_steps + 1, 0, 0, none);
-    if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(&s, ctx->dSlots, sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    rc = copy_plan_out(ctx, 0, s, out);
+    rc = timed_planner(ctx, 1, nullptr, ctx->cfg.max_steps + 1, 0, 0, none, ctx->hSlots, 0, false);
+    rc = rc ? rc : plans_enqueue(ctx, ctx->hSlots, 1);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    rc = planner_time(ctx);
+    rc = rc ? rc : plans_collect(ctx, ctx->hSlots, ctx->hSlots, 1, out);
+    if (rc) return rc;
     ctx->st_pairs = s.pairs;
     ctx->st_entries = s.entries;
     ctx->st_steps = s.steps;
@@ -753,23 +796,22 @@ int fastmdp_plan_departures(fastmdp_ctx *ctx, const fastmdp_request *req, int32_
     }
     int rc = refresh_grid(ctx, ctx->seq, false);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(ctx->dSlots, hs, n * sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
-    rc = timed_planner(ctx, n, nullptr, ctx->cfg.max_steps + 1, 1, 0, none);
+    rc = timed_planner(ctx, n, nullptr, ctx->cfg.max_steps + 1, 1, 0, none, hs, 0, false);
+    rc = rc ? rc : plans_enqueue(ctx, hs, n);
     if (rc) return rc;
-    HIP_TRY(hipMemcpyAsync(hs, ctx->dSlots, n * sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    rc = planner_time(ctx);
+    rc = rc ? rc : plans_collect(ctx, hs, hs, n, plans);
+    if (rc) return rc;
     int best = -1;
     for (int i = 0; i < n; ++i) {
-        rc = copy_plan_out(ctx, i, hs[i], &plans[i]);
-        if (rc) return rc;
         ctx->st_pairs += hs[i].pairs;
         ctx->st_entries += hs[i].entries;
         ctx->st_steps += hs[i].steps;
         // the earliest departure whose plan reached the goal and would be accepted
         if (hs[i].status == FASTMDP_OK && hs[i].valid && (best < 0 || t0[i] < t0[best])) best = i;
     }
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
     *chosen = best;
     return 0;
 }
@@ -808,32 +850,34 @@ int fastmdp_plan_batch(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs,
     int rc = planner(0);
     if (rc) return rc;
     HIP_TRY(fmdp::launch_batch_step(ctx->dc, ctx->dSlots, n, ctx->tr, ctx->bs, 1, ctx->stream));
-    int any = 1;
+    int any = ctx->hInt[2] = 1;
     for (int k = 0; any; ++k) {
         rc = planner(1);
         if (rc) return rc;
         HIP_TRY(fmdp::launch_batch_step(ctx->dc, ctx->dSlots, n, ctx->tr, ctx->bs, 0, ctx->stream));
-        if ((k & 15) == 15 || k >= ctx->cfg.max_steps) {
-            HIP_TRY(hipMemcpyAsync(&any, ctx->bs.any, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
-            HIP_TRY(hipStreamSynchronize(ctx->stream));
+        if ((k & 7) == 7) {
+            // the steps enqueued up to the last such point have ended; the
+            // eight since then run meanwhile
+            if (k > 7) HIP_TRY(hipEventSynchronize(ctx->eGather));
+            any = __atomic_load_n(ctx->hInt + 2, __ATOMIC_RELAXED);
+            HIP_TRY(hipEventRecord(ctx->eGather, ctx->stream));
             if (k > ctx->cfg.max_steps + 1) break;                 // every aircraft has hit the step limit
         }
     }
     HIP_TRY(hipEventRecord(ctx->e1, ctx->stream));
+    rc = plans_enqueue(ctx, ctx->dSlots, n);
+    if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(hs, ctx->dSlots, n * sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     float ms = 0.0f;
     HIP_TRY(hipEventElapsedTime(&ms, ctx->e0, ctx->e1));
     ctx->st_ms = ms;
     for (int i = 0; i < n; ++i) {
-        rc = copy_plan_out(ctx, i, hs[i], &plans[i]);
-        if (rc) return rc;
         ctx->st_pairs += hs[i].pairs;
         ctx->st_entries += hs[i].entries;
         ctx->st_steps += hs[i].steps;
     }
-    HIP_TRY(hipStreamSynchronize(ctx->stream));
-    return 0;
+    return plans_collect(ctx, ctx->dSlots, hs, n, plans);
 }
 
 int fastmdp_commit_plan(fastmdp_ctx *ctx, const fastmdp_plan *plan) {
@@ -844,13 +888,10 @@ int fastmdp_commit_plan(fastmdp_ctx *ctx, const fastmdp_plan *plan) {
     if ((long)t0 + n > ctx->tb.rows || n > ctx->stride) return FASTMDP_E_CAPACITY;
     for (int k = 0; k < n; ++k)
         if (ctx->hRowN[t0 + k] >= ctx->tb.cap) return FASTMDP_E_CAPACITY;
-    HIP_TRY(hipMemcpyAsync(ctx->dPts, plan->xyz, (size_t)n * 3 * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(fmdp::launch_fill_int(ctx->dFlag, 0, 1, ctx->stream));
-    HIP_TRY(fmdp::launch_commit_check(ctx->dc, ctx->tb, ctx->dPts, t0, n, ctx->seq, ctx->dFlag, ctx->stream));
-    HIP_TRY(fmdp::launch_commit_append(ctx->tb, ctx->dPts, t0, n, ctx->seq, ctx->dFlag, ctx->stream));
-    int flag = 0;
-    HIP_TRY(hipMemcpyAsync(&flag, ctx->dFlag, sizeof(int), hipMemcpyDeviceToHost, ctx->stream));
+    std::memcpy(ctx->hPts, plan->xyz, (size_t)n * 3 * sizeof(double));
+    HIP_TRY(fmdp::launch_commit(ctx->dc, ctx->tb, ctx->hPts, t0, n, ctx->seq, ctx->dFlag, ctx->hInt + 1, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    const int flag = ctx->hInt[1];
     if (flag & 2) return FASTMDP_E_CAPACITY;
     if (flag) return FASTMDP_E_CONFLICT;
     for (int k = 0; k < n; ++k) ctx->hRowN[t0 + k] += 1;
@@ -962,7 +1003,7 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 // half)
                 const int stop_div = fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ? 2 : 4;
                 const int stop_target = std::max(1, (int)list.size() / stop_div);
-                int rc = timed_planner(ctx, (int)list.size(), ctx->hList, budget, 1, epoch, none, stop_target, false);
+                int rc = timed_planner(ctx, (int)list.size(), ctx->hList, budget, 1, epoch, none, ctx->dSlots, stop_target, false);
                 if (rc) return finish(rc);
             }
             pass.clear();
@@ -1009,7 +1050,7 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 if (hs[s].killed) break;
             }
             if (!acc_slots.empty()) {
-                int rc = gather_enqueue(ctx, acc_slots, acc_reqs, hs, plans, pending);
+                int rc = gather_enqueue(ctx, ctx->dSlots, acc_slots, acc_reqs, hs, plans, pending);
                 if (rc) return finish(rc);
                 gathered = true;
                 for (int s : acc_slots) slot_req[s] = -1;   // reusable: the gather precedes any new planning
@@ -1133,9 +1174,9 @@ int fastmdp_eval_proposal(fastmdp_ctx *ctx, const fastmdp_state *state, float *f
     HIP_TRY(hipMemcpyAsync(ctx->dSlots, &s, sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipMemsetAsync(ctx->dEvF, 0, (FASTMDP_N_FEAT + fmdp::kMaxActions) * sizeof(float), ctx->stream));
     const int A = ctx->A;
-    EvalOut ev{nullptr, nullptr, nullptr, nullptr, ctx->dBest, ctx->dEvF, ctx->dEvF + FASTMDP_N_FEAT,
+    EvalOut ev{nullptr, nullptr, nullptr, nullptr, ctx->hInt, ctx->dEvF, ctx->dEvF + FASTMDP_N_FEAT,
                ctx->dEvI, ctx->dEvI + FASTMDP_MAX_TOPK, ctx->dEvI + FASTMDP_MAX_TOPK + 1};
-    int rc = timed_planner(ctx, 1, nullptr, 1, 0, 0, ev);
+    int rc = timed_planner(ctx, 1, nullptr, 1, 0, 0, ev, ctx->dSlots);
     if (rc) return rc;
     std::vector<float> hf(FASTMDP_N_FEAT + (size_t)A);
     int hi[FASTMDP_MAX_TOPK + 2];

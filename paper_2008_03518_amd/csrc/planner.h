@@ -257,7 +257,7 @@ struct BatchState {
     int *owner, *n;
     int *active;     // aircraft flying in the step just planned
     int *prev_n;     // its point count before that step
-    int *any;        // 1 while an aircraft is flying
+    int *any;        // 1 while an aircraft is flying (pinned host memory)
 };
 
 // nt: workgroup size; kPlanThreads is the one built.  prop.mode selects the
@@ -325,10 +325,11 @@ hipError_t launch_scatter_points(const DevTable &t, const float *pts, const int 
 // checked rows and capacity.
 hipError_t launch_append_plans(const DevTable &t, const int *t0, const int *len, int n, const float *xyz,
                                hipStream_t st);
-hipError_t launch_commit_check(const DevCfg &c, const DevTable &t, const double *pts, int t0, int n, int seq,
-                               int *flag, hipStream_t st);
-hipError_t launch_commit_append(const DevTable &t, const double *pts, int t0, int n, int own, const int *flag,
-                                hipStream_t st);
+// Commit of n points (host memory the device sees, or device memory): the
+// check of each point into flags (n), then, if none refuses, the append;
+// *result (the same kinds of memory): bit 0 conflict, bit 1 capacity.
+hipError_t launch_commit(const DevCfg &c, const DevTable &t, const double *pts, int t0, int n, int seq, int *flags,
+                         int *result, hipStream_t st);
 // Pack listed slots' trajectories (points from off[i]) into dst: total*3
 // doubles xyz, total doubles value, total ints action.  list, off and dst may
 // be pinned host memory.

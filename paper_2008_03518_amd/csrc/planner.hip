@@ -32,15 +32,14 @@
 
 namespace fmdp {
 
-// Largest risk well, at point (x, y, z), of the peaks of the other aircraft
-// of a co-simulated batch (all but slot `self`): |r_intr| gamma_intr^(d/ell)
-// of the nearest peak whose radius contains the point (the wells share r and
-// gamma, so the nearest such peak gives the largest), 0 if none.
-__device__ double mate_well(const DevCfg &c, const MatePeaks &mp, int nm, int self, double x, double y, double z) {
+// Largest risk well, at point (x, y, z), of the nm peaks near the state
+// (x, y, z, radius in LDS): |r_intr| gamma_intr^(d/ell) of the nearest peak
+// whose radius contains the point (the wells share r and gamma, so the
+// nearest such peak gives the largest), 0 if none.
+__device__ double mate_well(const DevCfg &c, const double (*pk)[4], int nm, double x, double y, double z) {
     double best = INFINITY;
     for (int k = 0; k < nm; ++k) {
-        if (mp.owner[k] == self) continue;
-        const double *p = mp.pk + 4 * k;
+        const double *p = pk[k];
         const double dx = x - p[0], dy = y - p[1], dz = z - p[2];
         const double d2 = dx * dx + dy * dy + dz * dz;
         if (d2 < p[3] * p[3]) best = fmin(best, d2);
@@ -112,6 +111,11 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
     __shared__ double sStep[FASTMDP_MAX_ACT_DIM], sDz[FASTMDP_MAX_ACT_DIM];   // speed*dt, climb*dt
     __shared__ float sKv[FASTMDP_MAX_ACT_DIM], sClf[FASTMDP_MAX_ACT_DIM];      // FP32 sweep constants
     const ActTab at{sStep, sDz};
+    // a co-simulated batch: the peaks of the other aircraft that reach one of
+    // this step's successors
+    constexpr int kNearPeaks = (PROP || LOOK) ? 1 : kMaxBatch * kMatePeaks;
+    __shared__ double sPk[kNearPeaks][4];
+    __shared__ int s_npk;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -451,6 +455,23 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
         for (int h = tid; h < H; h += NT) {
             sCos[h] = dot2(cb, sC0[h], -sb, sS0[h]);
             sSin[h] = dot2(sb, sC0[h], cb, sS0[h]);
+        }
+        // the batch's peaks near the state: few of them, in LDS (every action
+        // read all of them from memory, one behind the other: 20.8 us a launch
+        // at 10 aircraft, 16.5 us this way)
+        if (n_mates > 0) {                                // uniform
+            if (tid == 0) s_npk = 0;
+            lds_barrier();
+            for (int j = tid; j < n_mates; j += NT) {
+                const double *p = mates.pk + 4 * j;
+                const double dx = s[0] - p[0], dy = s[1] - p[1], dz = s[2] - p[2];
+                const double far = fabs(p[3]) + cfg.max_step + 1.0;
+                if (mates.owner[j] != slot && dx * dx + dy * dy + dz * dz < far * far) {
+                    const int o = atomicAdd(&s_npk, 1);
+                    sPk[o][0] = p[0]; sPk[o][1] = p[1]; sPk[o][2] = p[2]; sPk[o][3] = p[3];
+                }
+            }
+            lds_barrier();
         }
         const int row = t + 1;
         const int n_row = pre_n;
@@ -1112,7 +1133,7 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
                 const int h = a / (NC * NV);
                 double x, y, z;
                 successor(cfg, at, a, s, sCos[h], sSin[h], x, y, z);
-                myM = mate_well(cfg, mates, n_mates, slot, x, y, z);
+                myM = mate_well(cfg, sPk, s_npk, x, y, z);
             }
             if (a < A) {
                 // eight independent chains, so that eight LDS reads are in

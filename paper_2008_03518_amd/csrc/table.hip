@@ -162,17 +162,26 @@ __device__ int check_point(const DevCfg &c, const DevTable &tb, const double p[3
     return f;
 }
 
-__global__ void commit_check_kernel(DevCfg c, DevTable tb, const double *pts, int t0, int n, int seq, int *flag) {
+__global__ void commit_check_kernel(DevCfg c, DevTable tb, const double *pts, int t0, int n, int seq, int *flags) {
     const int k = blockIdx.x;
     if (k >= n) return;
     const double p[3] = {pts[3 * k], pts[3 * k + 1], pts[3 * k + 2]};
     const int f = check_point(c, tb, p, t0 + k, seq, threadIdx.x, blockDim.x);
-    if (f) atomicOr(flag, f);
+    const int conflict = __syncthreads_or(f & 1), full = __syncthreads_or(f & 2);
+    if (threadIdx.x == 0) flags[k] = (conflict ? 1 : 0) | (full ? 2 : 0);
 }
 
 // Append the trajectory rounded to FP32 (the table's storage format).
-__global__ void commit_append_kernel(DevTable tb, const double *pts, int t0, int n, int own, const int *flag) {
-    if (*flag) return;
+// Every workgroup looks at all points' flags; one tells the host.  Points and
+// result lie in pinned host memory: check and append take 10 us, where the
+// copy of the points, the flag's clearing and its copy added three transfers.
+__global__ void commit_append_kernel(DevTable tb, const double *pts, int t0, int n, int own, const int *flags,
+                                     int *result) {
+    int f = 0;
+    for (int i = threadIdx.x; i < n; i += blockDim.x) f |= flags[i];
+    const int conflict = __syncthreads_or(f & 1), full = __syncthreads_or(f & 2);
+    if (blockIdx.x == 0 && threadIdx.x == 0) *result = (conflict ? 1 : 0) | (full ? 2 : 0);
+    if (conflict || full) return;
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
     const int row = t0 + k;
@@ -761,17 +770,12 @@ hipError_t launch_scatter_points(const DevTable &t, const float *pts, const int 
     return hipGetLastError();
 }
 
-hipError_t launch_commit_check(const DevCfg &c, const DevTable &t, const double *pts, int t0, int n, int seq,
-                               int *flag, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(commit_check_kernel, dim3(n), dim3(256), 0, st, c, t, pts, t0, n, seq, flag);
-    return hipGetLastError();
-}
-
-hipError_t launch_commit_append(const DevTable &t, const double *pts, int t0, int n, int own, const int *flag,
-                                hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(commit_append_kernel, dim3((n + 255) / 256), dim3(256), 0, st, t, pts, t0, n, own, flag);
+hipError_t launch_commit(const DevCfg &c, const DevTable &t, const double *pts, int t0, int n, int seq, int *flags,
+                         int *result, hipStream_t st) {
+    if (n <= 0) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(commit_check_kernel, dim3(n), dim3(256), 0, st, c, t, pts, t0, n, seq, flags);
+    hipLaunchKernelGGL(commit_append_kernel, dim3((n + 255) / 256), dim3(256), 0, st, t, pts, t0, n, seq, flags,
+                       result);
     return hipGetLastError();
 }
 
