@@ -92,6 +92,7 @@ struct fastmdp_ctx {
     double *hIo = nullptr, *hPts = nullptr;
     int *hInt = nullptr;
     int *dFlag = nullptr;         // commit check: per point
+    int *dFeatWs = nullptr;       // fastmdp_features: grouping of the states by row (made when first used)
     DeathLog dl[2]{};                     // FCFS withdrawals: of the last pass and of the one running
     int *dRowNPre = nullptr, *dInsN = nullptr;   // acceptance-pass work buffers (fmdp::PassBufs)
     int4 *dIns = nullptr;
@@ -157,7 +158,7 @@ void free_all(fastmdp_ctx *c) {
     hipFree(c->dSlots);
     hipFree(c->tr.xyz); hipFree(c->tr.act); hipFree(c->tr.val); hipFree(c->tr.seen); hipFree(c->tr.top);
     hipFree(c->tr.ep); hipFree(c->tr.col); hipFree(c->tr.nd); hipFree(c->tr.seenw);
-    hipFree(c->dFlag);
+    hipFree(c->dFlag); hipFree(c->dFeatWs);
     if (c->hIo) hipHostFree(c->hIo);
     if (c->hSlots) hipHostFree(c->hSlots);
     if (c->hGather) hipHostFree(c->hGather);
@@ -1129,7 +1130,10 @@ int fastmdp_features(fastmdp_ctx *ctx, int32_t n, const double *states, const do
                      const int32_t *seqs, float *feat) {
     if (!ctx || n < 0 || (n > 0 && (!states || !goals || !rows || !seqs || !feat))) return FASTMDP_E_INVAL;
     std::lock_guard<std::mutex> lk(ctx->mu);
-    HIP_TRY(fmdp::launch_features(ctx->dc, ctx->tb, n, states, goals, rows, seqs, feat, ctx->stream));
+    if (n >= fmdp::kFeatGrouped && !ctx->dFeatWs &&
+        dev_alloc(&ctx->dFeatWs, fmdp::features_workspace(ctx->tb.rows)))
+        (void)hipGetLastError();                       // no memory for it: one workgroup per state
+    HIP_TRY(fmdp::launch_features(ctx->dc, ctx->tb, n, states, goals, rows, seqs, feat, ctx->dFeatWs, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     return 0;
 }

@@ -305,8 +305,16 @@ inline int range_planner_threads(const DevCfg &c, int nblk) {
 
 // features.hip: proposal features of n states (device arrays, see
 // fastmdp_features).
+// ws: features_workspace(rows) ints, or null (then one workgroup per state
+// whatever n).  From kFeatGrouped states on they are grouped by row, a chunk
+// at a time: a workgroup a state takes 5.7 us per 1000 states (51 us at 8000,
+// 93 us at 16383), the groups and their order 82 us at 16384 (a workgroup for
+// each CU; fewer states leave CUs idle at the same latency) and 114 us at
+// 100000.
+constexpr int kFeatChunk = 1 << 17, kFeatGrouped = 16384;
+size_t features_workspace(int n_rows);
 hipError_t launch_features(const DevCfg &c, const DevTable &t, int n, const double *states, const double *goals,
-                           const int *rows, const int *seqs, float *feat, hipStream_t st);
+                           const int *rows, const int *seqs, float *feat, int *ws, hipStream_t st);
 
 // mlp.hip: the planner's view of a network's weights.
 int mlp_weights(const fastmdp_mlp *m, PropNet *w);

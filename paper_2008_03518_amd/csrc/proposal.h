@@ -62,8 +62,8 @@ __device__ __forceinline__ void feat_reset(FeatAcc &f, int tid) {
 __device__ __forceinline__ void feat_point(FeatAcc &f, float qx, float qy, bool up, float w, float ux, float uy) {
     const float d = sqrtf(w);
     if (!(d < kFeatR)) return;
-    const float along = qx * ux + qy * uy;
-    const float cross = qy * ux - qx * uy;
+    const float along = fmaf(qx, ux, qy * uy);
+    const float cross = fmaf(qy, ux, -(qx * uy));
     const float phi = atan2f(cross, along);
     int k = (int)floorf((phi + (float)M_PI) * (float)(kSectors / (2.0 * M_PI)));
     k = k < 0 ? 0 : (k > kSectors - 1 ? kSectors - 1 : k);
@@ -81,8 +81,9 @@ __device__ __forceinline__ float feat_value(const FeatAcc &f, int i, const doubl
     if (i < 2 * kSectors) return __uint_as_float(f.near[i]);
     if (i < 4 * kSectors) return (float)min(f.cnt[i - 2 * kSectors], 4) * 0.25f;
     const double bx = g[0] - s[0], by = g[1] - s[1], bz = g[2] - s[2];
-    const double rh = sqrt(bx * bx + by * by);
-    const double d3 = sqrt(bx * bx + by * by + bz * bz);
+    const double h2 = __builtin_fma(bx, bx, by * by);
+    const double rh = sqrt(h2);
+    const double d3 = sqrt(__builtin_fma(bz, bz, h2));
     switch (i) {
         case 64: return (float)(rh / 10000.0);
         case 65: return (float)(bz / 500.0);
