@@ -962,18 +962,19 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 if (gathered) HIP_TRY(hipStreamWaitEvent(ctx->stream, ctx->eGather, 0));
                 HIP_TRY(hipMemcpyAsync(ctx->dSlots, hs, S * sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
             }
-            // plan the oldest running requests, one per compute unit (the
-            // planner's workgroups take a CU each; the range-query planner's
-            // two: it could hold four, but the oldest requests, which the later
-            // ones depend on, then step more slowly; measured: 3 % shorter
-            // FCFS passes with two), for up to `budget` steps: a
+            // plan the oldest running requests, two per compute unit (with the
+            // proposal or the window one: their workgroups take a CU each; the
+            // range-query planner could hold four, but the oldest requests,
+            // which the later ones depend on, then step more slowly; the full
+            // sweep: 78 ms a pass of 1000 requests at 3000 plans with two, 88
+            // with one), for up to `budget` steps: a
             // request that waits for the next launch plans against the plans its
             // predecessors finish in this one instead of re-planning after them
             list.clear();
             for (int s = 0; s < S; ++s)
                 if (slot_req[s] >= 0 && hs[s].status == fmdp::kRunning) list.push_back(s);
             const int per_launch =
-                ctx->n_cu * (fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ? fmdp::kRangeLaunchPerCU : 1);
+                ctx->n_cu * (ctx->prop.mode == FASTMDP_PROPOSE_NONE && ctx->dc.lookahead <= 1 ? fmdp::kLaunchPerCU : 1);
             if ((int)list.size() > per_launch) {
                 std::nth_element(list.begin(), list.begin() + per_launch, list.end(),
                                  [&](int a, int b) { return hs[a].req < hs[b].req; });
@@ -996,12 +997,12 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
                 // the launch ends once a quarter of its requests have finished:
                 // the others resume after the acceptance pass, with new requests
-                // in the freed compute units.  The range-query planner's launches
-                // hold two requests per CU, and few wait for one after the first
-                // launches, so the launch runs until half have finished (fewer
-                // acceptance passes; measured: about 10 % shorter FCFS passes
-                // than with a quarter, while the one-per-CU planners lose with
-                // half)
+                // in the freed compute units.  In the range-query planner's
+                // launches few requests wait for a place after the first ones, so
+                // they run until half have finished (fewer acceptance passes;
+                // measured: about 10 % shorter FCFS passes than with a quarter;
+                // the full sweep, whose steps cost more than a pass, takes 79 ms
+                // with a quarter and 91 with half)
                 const int stop_div = fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ? 2 : 4;
                 const int stop_target = std::max(1, (int)list.size() / stop_div);
                 int rc = timed_planner(ctx, (int)list.size(), ctx->hList, budget, 1, epoch, none, ctx->dSlots, stop_target, false);

@@ -10,10 +10,11 @@
 namespace fmdp {
 
 constexpr int kPlanThreads = 1024;  // planning workgroup: one request per CU, 16 wave64
+constexpr int kPairThreads = 512;   // full sweep of more requests than CUs: two per CU, 8 wave64 each
 constexpr int kPropThreads = 512;   // with the proposal path: 8 wave64, twice the registers per lane
 constexpr int kRangeThreads = 256;  // range-query planner: 4 wave64, up to four requests per CU
 constexpr int kRangePerCU = 4;      // range-query workgroups resident per CU (LDS and registers)
-constexpr int kRangeLaunchPerCU = 2;  // FCFS requests per CU in a range-query planner launch
+constexpr int kLaunchPerCU = 2;     // FCFS requests per CU in a launch (no proposal, no window)
 constexpr int kRangeThreadsSolo = 512;  // range-query planner alone on a CU: 8 wave64, one action per thread
 constexpr int kRangeMaxHeads = 64;  // headings the range-query planner takes (its LDS budget)
 constexpr int kMaxActions = 512;

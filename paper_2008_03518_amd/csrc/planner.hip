@@ -56,20 +56,25 @@ constexpr float kGoalBoundRel = 1e-4f;
 // Longest run of steps the proposal sits out after repeated fallbacks.
 constexpr int kMaxBackoff = 16;
 
-template <int NT>
+template <int NT, bool PROP>
 struct PlanGeom {
     static constexpr int NW = NT / 64;
-    static constexpr int TILE = 4096;                        // row entries per chunk (LDS tile)
+    // row entries per chunk (LDS tile): two workgroups of a pair share a CU's LDS
+    static constexpr int TILE = NT == kPairThreads && !PROP ? 2048 : 4096;
+    static constexpr int OCC = NT == kPropThreads && PROP ? 2 : 4;   // waves per SIMD (registers: 256 or 128)
     static constexpr int PRE = TILE / NT;                    // chunk entries per thread
     static constexpr int PRE4 = TILE / (4 * NT);             // 16-byte (four-entry) groups per thread
     static_assert(TILE % (4 * NT) == 0, "a chunk is a whole number of four-entry groups per thread");
 };
 
-template <int NT, int NC, int NV, int ZC, bool PROP, bool LOOK = false, bool CULL = false>
-__global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Slot *slots, const int *slot_list,
+// QUICK: many steps a launch, no single-step outputs, no batch -- the choice
+// without scoring every action (a variant of its own: its registers cost the
+// one-step launches 2 us each).
+template <int NT, int NC, int NV, int ZC, bool PROP, bool LOOK = false, bool CULL = false, bool QUICK = false>
+__global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(DevCfg cfg, DevTable tb, Slot *slots, const int *slot_list,
                                                      Traj tr, int budget, int validate, int epoch, EvalOut ev,
                                                      PropArgs prop, LaunchStop stop, MatePeaks mates) {
-    using Geo = PlanGeom<NT>;
+    using Geo = PlanGeom<NT, PROP>;
     constexpr int NW = Geo::NW, TILE = Geo::TILE, PRE = Geo::PRE, PRE4 = Geo::PRE4;
     constexpr int KMAX = FASTMDP_MAX_TOPK, HID = FASTMDP_MLP_HIDDEN;
     __shared__ float4 tile[TILE];               // staged plans; reused for the slice partial minima
@@ -113,9 +118,15 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
     const ActTab at{sStep, sDz};
     // a co-simulated batch: the peaks of the other aircraft that reach one of
     // this step's successors
-    constexpr int kNearPeaks = (PROP || LOOK) ? 1 : kMaxBatch * kMatePeaks;
+    constexpr int kNearPeaks = (PROP || LOOK || QUICK) ? 1 : kMaxBatch * kMatePeaks;
     __shared__ double sPk[kNearPeaks][4];
     __shared__ int s_npk;
+    // the waves' nearest-to-goal actions (two steps in turn): squared distance
+    // to the goal, successor, squared distance to the nearest plan; action,
+    // number of actions as near
+    static_assert(!QUICK || (!PROP && !LOOK), "the proposal and the window choose by themselves");
+    __shared__ double sR[QUICK ? 2 : 1][QUICK ? NW : 1][5];
+    __shared__ int sRa[QUICK ? 2 : 1][QUICK ? NW : 1][2];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -125,7 +136,7 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
     if (!eval && S.status != kRunning) return;          // a finished request (uniform: one slot per workgroup)
 
     const int H = cfg.n_head, A = cfg.n_actions;
-    const int n_mates = (!PROP && !LOOK && mates.n) ? *mates.n : 0;   // co-simulated batch peaks
+    const int n_mates = (!PROP && !LOOK && !QUICK && mates.n) ? *mates.n : 0;   // co-simulated batch peaks
     const int n_slices = NT / H;
     const int my_h = tid % H, my_slice = tid / H;
     const bool sweeper = tid < n_slices * H;
@@ -399,8 +410,9 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
         if (pre_n > 0) load_chunk(row, 0);
     }
 
-    auto flush_point = [&]() {                                  // thread 0
+    auto flush_point = [&]() {                                  // one thread
         if (!st_pend) return;
+        if (QUICK && st_pend == 2) st_pv[3] = goal_term(cfg, st_pv[0], st_pv[1], st_pv[2], g);
         const size_t p = pt_base + st_pi[0];
         tr.xyz[p * 3 + 0] = st_pv[0];
         tr.xyz[p * 3 + 1] = st_pv[1];
@@ -427,12 +439,12 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
     // would only add to the full sweep's cost
     int skip = 0, backoff = 1;
 
+    int n = st_n, par = 0;
+    double s[3] = {st_s[0], st_s[1], st_s[2]};
     for (;;) {
         if (st_status != kRunning) break;                 // uniform (LDS, after a barrier)
-        const int n = st_n;
         const int k = eval ? 0 : n - 1;                    // steps taken so far
         const int t = eval ? t0 : t0 + k;
-        const double s[3] = {st_s[0], st_s[1], st_s[2]};
         if (!eval) {
             const double ex = g[0] - s[0], ey = g[1] - s[1], ez = g[2] - s[2];
             if (sqrt(norm2(ex, ey, ez)) <= cfg.ell) {
@@ -1049,6 +1061,16 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
             for (int c = 0; c < NC; ++c)
 #pragma unroll
                 for (int v = 0; v < NV; ++v) acc[c][v] = INFINITY;
+            // Slices of the row: every thread's share of the sweep falls with
+            // their number, the fold of their minima grows with it (8 reads in
+            // flight); the sum is least near sqrt(5 n).  (Always all of them:
+            // 113 slices of 50 plans cost 1.7k cycles in the fold alone.)
+            const int es = min(n_slices, (int)sqrtf(5.0f * (float)n_row) + 1);
+            const bool sweeps = my_slice < es;
+            // the minima go behind the staged plans if they fit, else (behind a
+            // barrier) over them
+            const bool behind = single && 4 * n_row + es * A <= 4 * TILE;
+            float *red = reinterpret_cast<float *>(tile) + (behind ? 4 * TILE - es * A : 0);
             for (int base = 0; base < n_row; base += tcap) {
                 int nv;
                 if (base == 0 && staged) {
@@ -1065,13 +1087,13 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
                     }
                     n_vis += nv;
                     lds_barrier();
-                    if (base == 0 && tid == 0) flush_point();
+                    if (!QUICK && base == 0 && tid == 0) flush_point();
                 }
-                if (base == 0 && sweeper) {
+                if (base == 0 && sweeps) {
                     ch = (float)sCos[my_h];
                     sh = (float)sSin[my_h];
                 }
-                // whole rounds of 2 * n_slices plans, then one round with the
+                // whole rounds of 2 * es plans, then one round with the
                 // ragged tail (missing plans read as a plan at infinity)
                 auto sweep2 = [&](const float4 p0, const float4 p1) {
                     const float hq0 = fmaf(p0.x, ch, p0.y * sh);
@@ -1088,25 +1110,23 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
                         }
                     }
                 };
-                const int full = (nv / (2 * n_slices)) * (2 * n_slices);
-                if (sweeper) {
-                    for (int i = my_slice; i < full; i += 2 * n_slices) sweep2(tile[i], tile[i + n_slices]);
-                    if (full < nv) {
+                if (sweeps) {
+                    int i = my_slice;
+                    for (; i - my_slice + 2 * es <= nv; i += 2 * es) sweep2(tile[i], tile[i + es]);
+                    if (i - my_slice < nv) {
                         const float4 far = make_float4(0.0f, 0.0f, 0.0f, INFINITY);
-                        const int i = full + my_slice;
-                        sweep2(i < nv ? tile[i] : far, i + n_slices < nv ? tile[i + n_slices] : far);
+                        sweep2(i < nv ? tile[i] : far, i + es < nv ? tile[i + es] : far);
                     }
                 }
             }
-            lds_barrier();                                   // tile is reused below
+            if (!behind) lds_barrier();                      // the tile is free
             if (n_row == 0 && !eval && !staged) {
                 pre_n = next_count();
                 if (pre_n > 0) load_chunk(row + 1, 0);
             }
 
             // slice partial minima, one row of A per slice
-            float *red = reinterpret_cast<float *>(tile);
-            if (sweeper) {
+            if (sweeps) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
 #pragma unroll
@@ -1129,26 +1149,21 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
             // a co-simulated batch: the other aircraft's wells at this
             // action's successor
             double myM = 0.0;
-            if (n_mates > 0 && a < A) {
-                const int h = a / (NC * NV);
-                double x, y, z;
-                successor(cfg, at, a, s, sCos[h], sSin[h], x, y, z);
-                myM = mate_well(cfg, sPk, s_npk, x, y, z);
-            }
+            double myd2 = INFINITY;
+            if (QUICK && tid == NT - 64) flush_point();       // (the last wave: it has few actions or none)
             if (a < A) {
                 // eight independent chains, so that eight LDS reads are in
                 // flight instead of one
                 float m8[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) m8[j] = INFINITY;
-                // (with the range query, slices at or past the staged count
-                // swept nothing)
-                const int n_fold = CULL ? min(n_part, n_vis) : n_part;
+                // (slices at or past the staged count swept nothing)
+                const int n_fold = min(es, n_vis);
                 int q = 0;
-                for (; q + 8 <= n_fold; q += 8) {
+                for (; q < n_fold; q += 8) {
                     float r8[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) r8[j] = red[(q + j) * A + a];
+                    for (int j = 0; j < 8; ++j) r8[j] = red[min(q + j, n_fold - 1) * A + a];
                     // all eight values live at once: the reads are issued
                     // back to back rather than each after the previous one
                     asm volatile("" ::"v"(r8[0]), "v"(r8[1]), "v"(r8[2]), "v"(r8[3]), "v"(r8[4]), "v"(r8[5]),
@@ -1156,17 +1171,106 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
 #pragma unroll
                     for (int j = 0; j < 8; ++j) m8[j] = fminf(m8[j], r8[j]);
                 }
-                for (; q < n_fold; ++q) m8[0] = fminf(m8[0], red[q * A + a]);
                 const float m = fminf(fminf(fminf(m8[0], m8[1]), fminf(m8[2], m8[3])),
                                       fminf(fminf(m8[4], m8[5]), fminf(m8[6], m8[7])));
-                const double d2 = nearest_d2<NC, NV>(at, a, m);
-                sD2[a] = d2;
-                if (d2 > cfg.band_lo2 && d2 < cfg.band_hi2) {
+                myd2 = nearest_d2<NC, NV>(at, a, m);
+            }
+            // The nearest-to-goal action outside the wells.  Where the well's
+            // value at its radius exceeds the spread of a step's goal terms
+            // (detour_ok), actions inside a well score below every other; the
+            // goal term falls with the distance, so if one action is alone
+            // within the tie band's distance, it is the argmax, and its value
+            // is its goal term, which is computed while the next step runs.
+            // Ties, distances within kBand of the radius and terrain wells go to
+            // the scoring below.  Five requests planned in turn at 50 plans and
+            // 81 actions: 5.8 ms with every action scored, 4.2 ms (with the
+            // slices above).
+            if constexpr (QUICK) {
+                const double far = br + fabs(g[2] - s[2]);
+                if (cfg.detour_ok && br > 1e-50 && far <= cfg.run_dmax) {      // uniform
+                    double q2 = INFINITY, x = s[0], y = s[1], z = s[2];
+                    if (a < A) {
+                        const int h = a / (NC * NV);
+                        successor(cfg, at, a, s, sCos[h], sSin[h], x, y, z);
+                        const double ex = g[0] - x, ey = g[1] - y, ez = g[2] - z;
+                        if (myd2 > cfg.band_lo2 && !outside_box(cfg, x, y, z)) q2 = norm2(ex, ey, ez);
+                    }
+                    const double slack = cfg.run_margin * (2.0 * (far + cfg.max_step) + cfg.run_margin) * 1.0001;
+                    if (wave * 64 < A) {                     // uniform per wave
+                        const double d1 = -wave_max(-q2);
+                        const uint64_t first = __ballot(q2 == d1);
+                        const uint64_t close = __ballot(q2 <= d1 * (1.0 + 1e-14) + slack);
+                        if (lane == __builtin_ctzll(first)) {
+                            sR[par][wave][0] = d1;
+                            sR[par][wave][1] = x;
+                            sR[par][wave][2] = y;
+                            sR[par][wave][3] = z;
+                            sR[par][wave][4] = myd2;
+                            sRa[par][wave][0] = a;
+                            sRa[par][wave][1] = __popcll(close);
+                        }
+                    }
+                    if (tid == 0 && n_row == 0) take_stop();                 // no staging in this step
+                    if (!single) {
+                        pre_n = next_count();
+                        if (pre_n > 0) load_chunk(row + 1, 0);
+                    }
+                    lds_barrier();
+                    double d1 = INFINITY;
+                    int w1 = 0, close = 0;
+                    for (int w = 0; w * 64 < A; ++w) {
+                        const double d = sR[par][w][0];
+                        if (d < d1) {
+                            d1 = d;
+                            w1 = w;
+                        }
+                    }
+                    const double lim = d1 * (1.0 + 1e-14) + slack;
+                    for (int w = 0; w * 64 < A; ++w) close += sR[par][w][0] <= lim ? (w == w1 ? sRa[par][w][1] : 1) : 0;
+                    const double dn = sR[par][w1][4];
+                    x = sR[par][w1][1];
+                    y = sR[par][w1][2];
+                    z = sR[par][w1][3];
+                    const int best = sRa[par][w1][0];
+                    par ^= 1;
+                    if (d1 < INFINITY && close == 1 && dn >= cfg.band_hi2 &&
+                        (!tb.terr || z - terrain_height(tb, x, y) >= cfg.R_terr)) {          // uniform
+                        if (tid == 0) {
+                            st_pv[0] = x; st_pv[1] = y; st_pv[2] = z;
+                            st_pv[4] = dn;
+                            st_pi[0] = n; st_pi[1] = best; st_pi[2] = n_row; st_pi[3] = epoch; st_pi[4] = -1;
+                            st_pend = 2;                     // the value is still to come
+                            st_s[0] = x; st_s[1] = y; st_s[2] = z;
+                            st_n = n + 1;
+                            pairs += (long long)A * n_vis;
+                        }
+                        s[0] = x; s[1] = y; s[2] = z;
+                        n += 1;
+                        steps_here += 1;
+                        continue;
+                    }
+                } else {
+                    if (tid == 0 && n_row == 0) take_stop();
+                    if (!single) {
+                        pre_n = next_count();
+                        if (pre_n > 0) load_chunk(row + 1, 0);
+                    }
+                }
+            }
+            if (a < A) {
+                if (n_mates > 0) {
+                    const int h = a / (NC * NV);
+                    double x, y, z;
+                    successor(cfg, at, a, s, sCos[h], sSin[h], x, y, z);
+                    myM = mate_well(cfg, sPk, s_npk, x, y, z);
+                }
+                sD2[a] = myd2;
+                if (myd2 > cfg.band_lo2 && myd2 < cfg.band_hi2) {
                     atomicOr(&sBand[a >> 5], 1u << (a & 31));
                     myband = true;
                 } else {
                     const int h = a / (NC * NV);
-                    myr = score_action(cfg, tb, at, a, s, g, sCos[h], sSin[h], d2);
+                    myr = score_action(cfg, tb, at, a, s, g, sCos[h], sSin[h], myd2);
                     if (n_mates > 0 && myr.V > -INFINITY)       // the batch's wells join the penalties
                         myr.V = myr.G - fmax(fmax(myr.I, myM), myr.T);
                     myV = myr.V;
@@ -1214,7 +1318,7 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
                     if (ev.I) ev.I[a] = myr.I;
                     if (ev.T) ev.T[a] = myr.T;
                 }
-            } else if (!single) {
+            } else if (!QUICK && !single) {
                 pre_n = next_count();                            // in flight during the advance
                 if (pre_n > 0) load_chunk(row + 1, 0);
             }
@@ -1230,7 +1334,7 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
                 pairs += (long long)A * n_vis;                   // pairs with the plans this request sees
                 if (eval && ev.best) *ev.best = best;
                 if (!eval && best < 0) st_status = FASTMDP_NO_VALID_ACTION;
-                if (!eval && n_row == 0) take_stop();            // no staging in this step
+                if (!QUICK && !eval && n_row == 0) take_stop();   // no staging in this step
             }
             // top is kept when the choice is not the largest
             if constexpr (!PROP) {
@@ -1265,7 +1369,10 @@ __global__ __launch_bounds__(NT) void planner_kernel(DevCfg cfg, DevTable tb, Sl
         steps_here += 1;
         lds_barrier();
         if (eval) break;
+        n = st_n;
+        s[0] = st_s[0]; s[1] = st_s[1]; s[2] = st_s[2];
     }
+    __syncthreads();   // the last point pending
     if (tid == 0) flush_point();
     __syncthreads();   // st_status written by thread 0 on the way out of the loop; trajectory complete
 
@@ -1306,9 +1413,18 @@ static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, co
     else if (prop.mode == FASTMDP_PROPOSE_NONE && c.range_query)
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, false, true>), dim3(nblk),
                            dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
-    else if (prop.mode == FASTMDP_PROPOSE_NONE)
+    else if (prop.mode == FASTMDP_PROPOSE_NONE && (budget <= 1 || mates.n || ev.V || ev.best))
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false>), dim3(nblk), dim3(kPlanThreads), 0, st, c,
                            t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
+    else if (prop.mode == FASTMDP_PROPOSE_NONE && nblk > c.n_cu)
+        // two requests per CU: one sweeps while the other stages its row and
+        // chooses (of a 16 us step at 2700 plans and 360 actions the sweep is
+        // 10.7); no more requests than CUs step faster on 16 waves each
+        hipLaunchKernelGGL((planner_kernel<kPairThreads, NC, NV, ZC, false, false, false, true>), dim3(nblk),
+                           dim3(kPairThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
+    else if (prop.mode == FASTMDP_PROPOSE_NONE)
+        hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, false, false, true>), dim3(nblk),
+                           dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (c.range_query)
         hipLaunchKernelGGL((planner_kernel<kPropThreads, NC, NV, ZC, true, false, true>), dim3(nblk),
                            dim3(kPropThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
