@@ -99,7 +99,10 @@ typedef struct {
                                         compute unit).  0 takes, where allowed,
                                         512 for a launch of at most one request
                                         per compute unit and 256 for a larger
-                                        one, else 1024; the proposal path keeps
+                                        one, else 1024 (a full sweep's launch
+                                        of more requests than compute units: 512,
+                                        two per compute unit); the proposal path
+                                        keeps
                                         its own workgroup and single-step
                                         outputs and co-simulated batches the
                                         1024-thread one.  Every choice gives

@@ -974,7 +974,10 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
             for (int s = 0; s < S; ++s)
                 if (slot_req[s] >= 0 && hs[s].status == fmdp::kRunning) list.push_back(s);
             const int per_launch =
-                ctx->n_cu * (ctx->prop.mode == FASTMDP_PROPOSE_NONE && ctx->dc.lookahead <= 1 ? fmdp::kLaunchPerCU : 1);
+                ctx->n_cu * (fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ||
+                                     fmdp::uses_pairs(ctx->dc, ctx->prop.mode)
+                                 ? fmdp::kLaunchPerCU
+                                 : 1);
             if ((int)list.size() > per_launch) {
                 std::nth_element(list.begin(), list.begin() + per_launch, list.end(),
                                  [&](int a, int b) { return hs[a].req < hs[b].req; });

@@ -296,7 +296,12 @@ inline bool uses_range_planner(const DevCfg &c, int prop_mode) {
     return c.range_query && c.lookahead <= 1 && prop_mode == FASTMDP_PROPOSE_NONE && c.n_head <= kRangeMaxHeads &&
            c.planner_threads != kPlanThreads;
 }
-// Its workgroup size for a launch of nblk requests: as configured, else
+// A launch of the full sweep of more requests than CUs takes two per CU
+// (kPairThreads) unless the configuration asks for kPlanThreads.
+inline bool uses_pairs(const DevCfg &c, int prop_mode) {
+    return !c.range_query && c.lookahead <= 1 && prop_mode == FASTMDP_PROPOSE_NONE && c.planner_threads != kPlanThreads;
+}
+// The range-query planner's workgroup size for a launch of nblk requests: as configured, else
 // one request per CU on kRangeThreadsSolo threads when the launch holds no
 // more requests than CUs, two to four per CU on kRangeThreads otherwise.
 inline int range_planner_threads(const DevCfg &c, int nblk) {

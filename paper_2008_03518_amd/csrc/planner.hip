@@ -1433,7 +1433,7 @@ static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, co
     else if (prop.mode == FASTMDP_PROPOSE_NONE && (budget <= 1 || mates.n || ev.V || ev.best))
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false>), dim3(nblk), dim3(kPlanThreads), 0, st, c,
                            t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
-    else if (prop.mode == FASTMDP_PROPOSE_NONE && nblk > c.n_cu)
+    else if (uses_pairs(c, prop.mode) && nblk > c.n_cu)
         // two requests per CU: one sweeps while the other stages its row and
         // chooses (of a 16 us step at 2700 plans and 360 actions the sweep is
         // 10.7); no more requests than CUs step faster on 16 waves each
