@@ -18,7 +18,9 @@
 //      terrain clearance well, value = goal - max(penalties), box mask
 //      (kernels "Process positive rewards", "Process negative terrain
 //      rewards", "Compute value");
-//   5. argmax by wavefront shuffle reductions ("Select best action");
+//   5. argmax by wavefront shuffle reductions ("Select best action"); in
+//      launches of many steps, 4 and 5 run only where the distances to the
+//      goal and to the nearest plan do not decide the action;
 //   6. state advance, goal capture, collision checks and trajectory append
 //      ("Determine terminal state").
 #include "planner.h"
@@ -1393,7 +1395,7 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
     if (tid == 0) flush_point();
     __syncthreads();   // st_status written by thread 0 on the way out of the loop; trajectory complete
 
-    // Commit validation (shared with the range-query planner)
+    // Commit validation
     if (!eval && validate && st_status == FASTMDP_OK) {
         const int bad = __syncthreads_or(validate_points<NT / 64>(cfg, tb, tr, pt_base, t0, st_n, seq));
         if (tid == 0) S.valid = bad == 0;
