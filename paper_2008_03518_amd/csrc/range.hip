@@ -30,6 +30,7 @@
 //   Measured (MI355X, 3000 plans, 360 actions): a request alone 3.5 -> 0.30 us
 // a step; the 1000-request stream's planner time 22.3 -> 9.6 ms.
 #include "planner.h"
+#include "row_window.h"
 #include "score.h"
 #include "wave.h"
 
@@ -59,7 +60,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     constexpr int NW = NT / 64;
     constexpr int TILE = NT;                     // staged entries per round: one candidate per thread
     constexpr int APT = kMaxActions / NT;        // actions per thread
-    constexpr int RUN = 16;                      // steps of a run: four lanes of the checking wave each
+    constexpr int RUN = kRunSteps;               // steps of a run: four lanes of the checking wave each
     constexpr int DS = 8;                        // steps of a detour batch
     constexpr int DL = 32;                       // entries listed per detour step
     constexpr int RING = 128;                    // points on their way to the trajectory
@@ -97,7 +98,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     __shared__ int sNb[2], sAg[2];
     __shared__ float sMg[2][RUN], sMt[2][RUN];
     __shared__ int sNg[2][RUN], sNt[2][RUN], sOk[2][RUN];
-    __shared__ int sCnt[128], sGn[128];                  // entry counts and indexed columns of rows wb .. wb + 127, by row % 128
+    __shared__ int sCnt[kCountRows], sGn[kCountRows];    // entry counts and indexed columns of rows wb .. wb + 127
     const ActTab at{sStep, sDz};
 
     const int tid = threadIdx.x;
@@ -173,22 +174,22 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     }
 
     // Entry counts and indexed columns of 128 rows from wb on (the table does
-    // not change during a launch), 64 rows at a time by one wave, a full 64
-    // rows before they are read
+    // not change during a launch), 64 rows at a time by one wave
+    // (row_window.h)
     int wb = t0 + n;
     auto read_counts = [&](int first) {
         const int r = first + lane;
         const bool in = r >= 0 && r < tb.rows;
-        sCnt[r & 127] = in ? min(tb.rowN[r], tb.cap) : 0;
-        sGn[r & 127] = in ? tb.gn[r] : 0;
+        sCnt[count_slot(r)] = in ? min(tb.rowN[r], tb.cap) : 0;
+        sGn[count_slot(r)] = in ? tb.gn[r] : 0;
     };
-    if (wave < 2) read_counts(wb + 64 * wave);
-    auto row_count = [&](int row) { return sCnt[row & 127]; };
-    auto row_indexed = [&](int row) { return sGn[row & 127]; };
-    auto shift_counts = [&](int row) {                    // uniform: the rows before `row` are not read again
-        if (row - wb >= 64) {
-            if (wave == NW - 1) read_counts(wb + 128);
-            wb += 64;
+    if (wave < 2) read_counts(wb + kCountLoad * wave);
+    auto row_count = [&](int row) { return sCnt[count_slot(row)]; };
+    auto row_indexed = [&](int row) { return sGn[count_slot(row)]; };
+    auto shift_counts = [&](int row) {                    // uniform; `row`: the next batch's first
+        if (count_load_due(wb, row)) {
+            if (wave == NW - 1) read_counts(wb + kCountRows);
+            wb += kCountLoad;
         }
     };
     // The exact test of the range query for one entry (x, y, z, visibility)
