@@ -29,6 +29,7 @@
 // time, a run's values evaluated 64 at a time.
 //   Measured (MI355X, 3000 plans, 360 actions): a request alone 3.5 -> 0.30 us
 // a step; the 1000-request stream's planner time 22.3 -> 9.6 ms.
+#include "bearing.h"
 #include "planner.h"
 #include "row_window.h"
 #include "score.h"
@@ -379,23 +380,15 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 }
                 for (int i = 0; i < nb; ++i) {            // uniform
                     // one step of all three components: the horizontal
-                    // distance by Goldschmidt's iteration and the quotients
-                    // b / br from the same reciprocal square root with one
-                    // exact remainder each, rounded as the square root and
-                    // the divisions of the single step round (r2 is far from
+                    // distance and the quotients b / br from one reciprocal
+                    // square root, rounded as the square root and the
+                    // divisions of the single step (bearing.h; r2 is far from
                     // the ends of the range: checked with the step)
                     const double b = g_l - s_l;
                     const double bx = dpp_bcast_f64<0>(b), by = dpp_bcast_f64<1>(b);
                     const double r2 = dot2(bx, bx, by, by);
-                    const double y = __builtin_amdgcn_rsq(r2);
-                    double a = r2 * y, h = 0.5 * y;
-                    const double e = __builtin_fma(-h, a, 0.5);
-                    a = __builtin_fma(a, e, a);
-                    h = __builtin_fma(h, e, h);
-                    a = __builtin_fma(__builtin_fma(-a, a, r2), h, a);
-                    const double br = __builtin_fma(__builtin_fma(-a, a, r2), h, a);
-                    const double inv = h + h, q0 = b * inv;
-                    const double q = __builtin_fma(__builtin_fma(-br, q0, b), inv, q0);
+                    const Bearing v = bearing(r2, __builtin_amdgcn_rsq(r2));
+                    const double br = v.br, q = bearing_quotient(b, v);
                     s_l = comp == 2 ? s_l + c_dz : __builtin_fma(v_step, q, s_l);
                     if (lane < 3) {
                         sQ[p][i][lane] = lane == 2 ? br : q;
@@ -657,17 +650,8 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                 const double bx = g[0] - x, by = g[1] - y, bz = g[2] - z;
                 const double r2 = dot2(bx, bx, by, by), e2 = __builtin_fma(bz, bz, r2);
                 // the direction, as a run's chain has it
-                const double yq = __builtin_amdgcn_rsq(r2);
-                double aq = r2 * yq, hq2 = 0.5 * yq;
-                const double eq = __builtin_fma(-hq2, aq, 0.5);
-                aq = __builtin_fma(aq, eq, aq);
-                hq2 = __builtin_fma(hq2, eq, hq2);
-                aq = __builtin_fma(__builtin_fma(-aq, aq, r2), hq2, aq);
-                const double br = __builtin_fma(__builtin_fma(-aq, aq, r2), hq2, aq);
-                const double inv = hq2 + hq2;
-                const double cx0 = bx * inv, sx0 = by * inv;
-                const double cb = __builtin_fma(__builtin_fma(-br, cx0, bx), inv, cx0);
-                const double sb = __builtin_fma(__builtin_fma(-br, sx0, by), inv, sx0);
+                const Bearing dir = bearing(r2, __builtin_amdgcn_rsq(r2));
+                const double br = dir.br, cb = bearing_quotient(bx, dir), sb = bearing_quotient(by, dir);
                 const double far = br + fabs(bz);
                 if (!(e2 > ell2_hi && r2 > 1e-100 && far <= cfg.run_dmax)) break;
                 // this thread's actions: squared distance to the goal, and
