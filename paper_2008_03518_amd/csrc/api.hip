@@ -1273,12 +1273,14 @@ int fastmdp_load_table(fastmdp_ctx *ctx, const char *path) {
     const int cap = ctx->tb.cap;
     std::vector<float> buf((size_t)cap * 3);
     std::vector<int> own((size_t)cap, -1), alive((size_t)cap, fmdp::kAlive);
-    for (int r = 0; r < rows; ++r) {
+    ctx->grid_ok = false;                              // rows are overwritten from here on
+    int rc = 0;
+    for (int r = 0; r < rows && !rc; ++r) {
         const int m = rowN[r];
         if (!m) continue;
         if (std::fread(buf.data(), sizeof(float), (size_t)m * 3, f) != (size_t)m * 3) {
-            std::fclose(f);
-            return FASTMDP_E_IO;
+            rc = FASTMDP_E_IO;
+            break;
         }
         const size_t off = (size_t)r * cap;
         float *dst[3] = {ctx->tb.X, ctx->tb.Y, ctx->tb.Z};
@@ -1289,19 +1291,17 @@ int fastmdp_load_table(fastmdp_ctx *ctx, const char *path) {
         ok = ok && hipMemcpy(ctx->tb.vis + off, own.data(), m * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
         ok = ok && hipMemcpy(ctx->tb.own + off, own.data(), m * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
         ok = ok && hipMemcpy(ctx->tb.dead + off, alive.data(), m * sizeof(int), hipMemcpyHostToDevice) == hipSuccess;
-        if (!ok) {
-            std::fclose(f);
-            return FASTMDP_E_DEVICE;
-        }
+        if (!ok) rc = FASTMDP_E_DEVICE;
     }
     std::fclose(f);
-    if (hipMemcpy(ctx->tb.rowN, rowN.data(), rows * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
-        return FASTMDP_E_DEVICE;
-    if (ctx->tb.Q) {
-        HIP_TRY(fmdp::launch_quantise_table(ctx->tb, ctx->stream));
-        HIP_TRY(hipStreamSynchronize(ctx->stream));
-    }
-    ctx->grid_ok = false;
+    if (!rc && hipMemcpy(ctx->tb.rowN, rowN.data(), rows * sizeof(int), hipMemcpyHostToDevice) != hipSuccess)
+        rc = FASTMDP_E_DEVICE;
+    // the 16-bit coordinates follow the points, also of the rows read before
+    // a file breaks off
+    if (ctx->tb.Q && (fmdp::launch_quantise_table(ctx->tb, ctx->stream) != hipSuccess ||
+                      hipStreamSynchronize(ctx->stream) != hipSuccess))
+        rc = rc ? rc : FASTMDP_E_DEVICE;
+    if (rc) return rc;
     ctx->hRowN.swap(rowN);
     ctx->n_plans = hdr[2];
     return 0;
