@@ -71,8 +71,10 @@ struct PlanGeom {
 
 // QUICK: many steps a launch, no single-step outputs, no batch -- the choice
 // without scoring every action (a variant of its own: its registers cost the
-// one-step launches 2 us each).
-template <int NT, int NC, int NV, int ZC, bool PROP, bool LOOK = false, bool CULL = false, bool QUICK = false>
+// one-step launches 2 us each).  MATES: the wells of a co-simulated batch
+// (their registers cost the range query's steps 4 %).
+template <int NT, int NC, int NV, int ZC, bool PROP, bool LOOK = false, bool CULL = false, bool QUICK = false,
+          bool MATES = false>
 __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(DevCfg cfg, DevTable tb, Slot *slots, const int *slot_list,
                                                      Traj tr, int budget, int validate, int epoch, EvalOut ev,
                                                      PropArgs prop, LaunchStop stop, MatePeaks mates) {
@@ -120,13 +122,13 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
     const ActTab at{sStep, sDz};
     // a co-simulated batch: the peaks of the other aircraft that reach one of
     // this step's successors
-    constexpr int kNearPeaks = (PROP || LOOK || QUICK) ? 1 : kMaxBatch * kMatePeaks;
+    constexpr int kNearPeaks = MATES ? kMaxBatch * kMatePeaks : 1;
     __shared__ double sPk[kNearPeaks][4];
     __shared__ int s_npk;
     // the waves' nearest-to-goal actions (two steps in turn): squared distance
     // to the goal, successor, squared distance to the nearest plan; action,
     // number of actions as near
-    static_assert(!QUICK || (!PROP && !LOOK), "the proposal and the window choose by themselves");
+    static_assert(!QUICK || (!PROP && !LOOK && !MATES), "the proposal, the window and the batch choose by themselves");
     __shared__ double sR[QUICK ? 2 : 1][QUICK ? NW : 1][5];
     __shared__ int sRa[QUICK ? 2 : 1][QUICK ? NW : 1][2];
 
@@ -138,7 +140,7 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
     if (!eval && S.status != kRunning) return;          // a finished request (uniform: one slot per workgroup)
 
     const int H = cfg.n_head, A = cfg.n_actions;
-    const int n_mates = (!PROP && !LOOK && !QUICK && mates.n) ? *mates.n : 0;   // co-simulated batch peaks
+    const int n_mates = (MATES && mates.n) ? *mates.n : 0;   // co-simulated batch peaks
     const int n_slices = NT / H;
     const int my_h = tid % H, my_slice = tid / H;
     const bool sweeper = tid < n_slices * H;
@@ -488,7 +490,9 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
             lds_barrier();
         }
         const int row = t + 1;
-        const int n_row = pre_n;
+        // (with the full sweep in a scalar register, and the slices below with
+        // it; the range query's kernel is the faster without)
+        const int n_row = CULL ? pre_n : __builtin_amdgcn_readfirstlane(pre_n);
         entries += n_row;                                 // (thread 0's count is the one kept)
         const size_t rb = (size_t)row * tb.cap;
         const bool single = n_row <= tcap;
@@ -1083,12 +1087,16 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
             // Slices of the row: every thread's share of the sweep falls with
             // their number, the fold of their minima grows with it (8 reads in
             // flight); the sum is least near sqrt(5 n).  (Always all of them:
-            // 113 slices of 50 plans cost 1.7k cycles in the fold alone.)
-            const int es = min(n_slices, (int)sqrtf(5.0f * (float)n_row) + 1);
+            // 113 slices of 50 plans cost 1.7k cycles in the fold alone.)  The
+            // range query stages few plans of a row: its fold stops at their
+            // number, and neither rule pays there.
+            const int es = CULL ? n_slices
+                                : __builtin_amdgcn_readfirstlane(
+                                      min(n_slices, (int)__builtin_amdgcn_sqrtf(5.0f * (float)n_row) + 1));
             const bool sweeps = my_slice < es;
             // the minima go behind the staged plans if they fit, else (behind a
             // barrier) over them
-            const bool behind = single && 4 * n_row + es * A <= 4 * TILE;
+            const bool behind = !CULL && single && 4 * n_row + es * A <= 4 * TILE;
             float *red = reinterpret_cast<float *>(tile) + (behind ? 4 * TILE - es * A : 0);
             for (int base = 0; base < n_row; base += tcap) {
                 int nv;
@@ -1176,13 +1184,14 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
                 float m8[8];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) m8[j] = INFINITY;
-                // (slices at or past the staged count swept nothing)
+                // (slices at or past the staged count swept nothing: with the
+                // range query a handful of them are left, one clamped round)
                 const int n_fold = min(es, n_vis);
                 int q = 0;
-                for (; q < n_fold; q += 8) {
+                for (; CULL ? q < n_fold : q + 8 <= n_fold; q += 8) {
                     float r8[8];
 #pragma unroll
-                    for (int j = 0; j < 8; ++j) r8[j] = red[min(q + j, n_fold - 1) * A + a];
+                    for (int j = 0; j < 8; ++j) r8[j] = red[(CULL ? min(q + j, n_fold - 1) : q + j) * A + a];
                     // all eight values live at once: the reads are issued
                     // back to back rather than each after the previous one
                     asm volatile("" ::"v"(r8[0]), "v"(r8[1]), "v"(r8[2]), "v"(r8[3]), "v"(r8[4]), "v"(r8[5]),
@@ -1190,6 +1199,8 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
 #pragma unroll
                     for (int j = 0; j < 8; ++j) m8[j] = fminf(m8[j], r8[j]);
                 }
+                if (!CULL)
+                    for (; q < n_fold; ++q) m8[0] = fminf(m8[0], red[q * A + a]);
                 const float m = fminf(fminf(fminf(m8[0], m8[1]), fminf(m8[2], m8[3])),
                                       fminf(fminf(m8[4], m8[5]), fminf(m8[6], m8[7])));
                 myd2 = nearest_d2<NC, NV>(at, a, m);
@@ -1429,12 +1440,15 @@ static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, co
     else if (c.lookahead > 1)
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, true>), dim3(nblk), dim3(kPlanThreads), 0,
                            st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
+    else if (prop.mode == FASTMDP_PROPOSE_NONE && c.range_query && mates.n)
+        hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, false, true, false, true>), dim3(nblk),
+                           dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (prop.mode == FASTMDP_PROPOSE_NONE && c.range_query)
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, false, true>), dim3(nblk),
                            dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (prop.mode == FASTMDP_PROPOSE_NONE && (budget <= 1 || mates.n || ev.V || ev.best))
-        hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false>), dim3(nblk), dim3(kPlanThreads), 0, st, c,
-                           t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
+        hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, false, false, false, true>), dim3(nblk),
+                           dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (uses_pairs(c, prop.mode) && nblk > c.n_cu)
         // two requests per CU: one sweeps while the other stages its row and
         // chooses (of a 16 us step at 2700 plans and 360 actions the sweep is
