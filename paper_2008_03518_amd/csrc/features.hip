@@ -105,9 +105,29 @@ __global__ __launch_bounds__(kFeatThreads) void features_kernel(DevCfg c, DevTab
 // its own).
 __device__ __forceinline__ int feat_bin(int row, int n_rows) { return row >= 0 && row < n_rows ? row : n_rows; }
 
+// The ranks' atomics on one row go one behind the other (11 ns each: 100000
+// states of one row took 1.1 ms), so a wave takes one for all of its states
+// of a row that many share, for the first such rows it holds; rows that few
+// share are counted one by one.
 __global__ void feat_rank_kernel(int n, const int *__restrict__ rows, int n_rows, int *count, int *rank) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) rank[i] = atomicAdd(&count[feat_bin(rows[i] + 1, n_rows)], 1);
+    constexpr int kShared = 8, kTries = 4;                // states of a row in the wave; rows tried
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, lane = threadIdx.x & 63;
+    int bin = i < n ? feat_bin(rows[i] + 1, n_rows) : -1;
+    uint64_t open = __ballot(bin >= 0);                   // states without a rank whose row was not tried
+    for (int q = 0; q < kTries && open; ++q) {            // uniform
+        const int lead = __builtin_ctzll(open), row = __shfl(bin, lead);
+        const uint64_t same = __ballot(bin == row);
+        open &= ~same;
+        if (__popcll(same) < kShared) continue;
+        int first = 0;
+        if (lane == lead) first = atomicAdd(&count[row], __popcll(same));
+        first = __shfl(first, lead);
+        if (bin == row) {
+            rank[i] = first + __popcll(same & ((1ull << lane) - 1));
+            bin = -1;
+        }
+    }
+    if (bin >= 0) rank[i] = atomicAdd(&count[bin], 1);
 }
 
 __global__ __launch_bounds__(1024) void feat_offset_kernel(int bins, const int *__restrict__ count, int *off) {
