@@ -210,6 +210,7 @@ void make_devcfg(const fastmdp_config &c, DevCfg &d) {
     d.r_intr = c.r_intr; d.R_intr = c.R_intr; d.gamma_intr = c.gamma_intr;
     d.R_sep = c.R_sep;
     d.r_terr = c.r_terr; d.R_terr = c.R_terr; d.gamma_terr = c.gamma_terr;
+    d.clear_terr = std::max(c.R_terr, 0.0);
     d.log_gamma = std::log(c.gamma);
     d.log_gamma_intr = std::log(c.gamma_intr);
     d.log_gamma_terr = std::log(c.gamma_terr);

@@ -68,6 +68,8 @@ struct DevCfg {
                                          // run_step: the longest action step in the same units
     int run_v, run_ok;
     int detour_ok;                       // an action inside a well never beats one outside every well
+    double clear_terr;                   // terrain clearance of a step that the goal term decides: clear of
+                                         // the terrain well, and not below the surface (max(R_terr, 0))
     int planner_threads;                 // full-sweep path: 0 (automatic), kRangeThreads, kRangeThreadsSolo,
                                          // kPlanThreads
     int n_cu;                            // compute units of the device

@@ -1264,7 +1264,7 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
                     const int best = sRa[par][w1][0];
                     par ^= 1;
                     if (d1 < INFINITY && close == 1 && dn >= cfg.band_hi2 &&
-                        (!tb.terr || z - terrain_height(tb, x, y) >= cfg.R_terr)) {          // uniform
+                        (!tb.terr || z - terrain_height(tb, x, y) >= cfg.clear_terr)) {          // uniform
                         if (tid == 0) {
                             st_pv[0] = x; st_pv[1] = y; st_pv[2] = z;
                             st_pv[4] = dn;

@@ -449,7 +449,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                             good = good && (q == ag || d2h > lim) && d2o > lim;
                         }
                     }
-                    if (tb.terr) good = good && nz - terrain_height(tb, nx, ny) >= cfg.R_terr;
+                    if (tb.terr) good = good && nz - terrain_height(tb, nx, ny) >= cfg.clear_terr;
                     // the indexed entries near the state, every fourth of its
                     // cells' records
                     const float ch = (float)cb, sh = (float)sb, kvv = sKv[cfg.run_v], clv = sClf[ag / NV];
@@ -747,7 +747,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                         dn = -wave_max(-dd);
                         if (!(dn >= cfg.R_intr * cfg.R_intr)) break;
                     }
-                    if (tb.terr && !(pz - terrain_height(tb, px, py) >= cfg.R_terr)) break;
+                    if (tb.terr && !(pz - terrain_height(tb, px, py) >= cfg.clear_terr)) break;
                 } else {
                     // several come as near (the two headings beside a plan on
                     // the track): their goal terms, then the single step's
@@ -764,7 +764,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
                         V[q] = goal_term(cfg, ux, uy, uz, g);
                         v1 = fmax(v1, V[q]);
                         bad = bad || !(dnq[q] >= cfg.band_hi2) ||
-                              (tb.terr && !(uz - terrain_height(tb, ux, uy) >= cfg.R_terr));
+                              (tb.terr && !(uz - terrain_height(tb, ux, uy) >= cfg.clear_terr));
                     }
                     v1 = wave_max(v1);
                     const uint64_t undecided = __ballot(bad);
