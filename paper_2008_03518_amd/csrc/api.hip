@@ -261,12 +261,12 @@ void make_devcfg(const fastmdp_config &c, DevCfg &d) {
     d.run_ok = d.abs_r_goal > 0.0 && c.tie_rel <= 1e-3 ? 1 : 0;
     d.run_c1 = c.n_head > 1 ? std::cos(2.0 * M_PI / c.n_head) : -1e9;
     // half-widths of the box test on 16-bit coordinates: the staging radius
-    // plus both roundings (half a step each), the FP32 arithmetic's and the
-    // FP32 state's (under a step together)
+    // plus both roundings (half a step each), the FP32 arithmetic's (under a
+    // step) and the FP32 state's (2^-24 of the coordinates)
     d.run_r = d.run_w = d.run_step = 0u;
     for (int k = 0; k < 2; ++k) {
         const double scale = 65535.0 / (c.box_max[k] - c.box_min[k]);
-        const double r = std::ceil(std::sqrt((double)d.cull_r2) * 1.001 * scale) + 3.0;
+        const double r = std::ceil((std::sqrt((double)d.cull_r2) * 1.001 + max_abs * 1e-6) * scale) + 3.0;
         const double m = std::ceil(d.max_step * scale);
         const bool fits = r > 0.0 && m >= 0.0 && r + 32.0 * m < 32000.0;
         if (!fits) d.run_ok = 0;

@@ -55,3 +55,27 @@ def test_flight_into_the_surface():
     assert want.status == fm.REJECT_TERRAIN
     for plans in out:
         _same(want, plans[0])
+
+
+@pytest.mark.parametrize("at", [0.0, 2.5e7])
+def test_entries_at_the_staging_radius(at):
+    """Plans that fly ahead and behind at the staging radius less 0 to 2 m,
+    in a box whose coordinates FP32 holds to 2 m (the flight's lie almost 1 m
+    off theirs): every planner counts the same entries within the radius."""
+    cfg = S.cfg_large_actions()
+    cfg.R_intr = 151.0
+    cfg.box_min, cfg.box_max = (at, at, 0.0), (at + 10000.0, at + 10000.0, 1500.0)
+    step = max(cfg.speed) * cfg.dt
+    reach = max(cfg.R_intr, cfg.R_sep) + 2.0 + np.hypot(max(cfg.speed), max(cfg.climb)) * cfg.dt
+    o, g = np.array([at + 1000.95, at + 3000.0, 400.0]), np.array([at + 9000.0, at + 3000.0, 400.0])
+    rows = 380
+    k = np.arange(rows)[:, None]
+    tracks = [o + [d, 0.0, 0.0] + (k - 1) * np.array([step, 0.0, 0.0])     # at row t + 1, d off the state at row t
+              for e in np.linspace(-0.1, 2.0, 12) for d in (reach - e, e - reach)]
+    known = S.Plans(np.zeros(len(tracks), np.int32), np.full(len(tracks), rows, np.int32),
+                    np.concatenate(tracks).astype(np.float32))
+    out, pairs = _plans(cfg, known, [(o, g, 0)])
+    for plans in out[1:]:
+        _same(out[0][0], plans[0])
+    print(pairs, flush=True)
+    assert pairs[0][1] > 0 and all(p == pairs[0][1] for _, p in pairs)
