@@ -139,6 +139,7 @@ int dev_alloc(T **p, size_t n) {
     *p = nullptr;
     if (n == 0) return 0;
     if (hipMalloc(reinterpret_cast<void **>(p), n * sizeof(T)) != hipSuccess) {
+        (void)hipGetLastError();           // reported here, not by the next launch
         *p = nullptr;
         return FASTMDP_E_NOMEM;
     }
@@ -362,44 +363,87 @@ struct PendingPlans {
 
 constexpr size_t kPointBytes = 4 * sizeof(double) + sizeof(int);      // a gathered point
 
-// The pinned gather buffer, grown to `bytes` (no copy into it is in flight).
+// A call that returns early waits for what it has enqueued: the kernels read
+// and write the context's pinned memory in place, and the next call fills it
+// anew.  (Behind the context's lock, so that the lock is held meanwhile.)
+struct Drain {
+    fastmdp_ctx *c;
+    bool done = false;                     // nothing is left in flight
+    ~Drain() {
+        if (done) return;
+        (void)hipStreamSynchronize(c->stream);
+        (void)hipStreamSynchronize(c->gstream);
+    }
+};
+
+// The pinned gather buffer, grown to `bytes` (no copy into it is in flight);
+// without memory for that the one there is stays.
 int gather_reserve(fastmdp_ctx *c, size_t bytes) {
     if (bytes <= c->gather_cap) return 0;
-    const size_t cap = std::max(bytes, 2 * c->gather_cap);
+    size_t cap = std::max(bytes, 2 * c->gather_cap);
+    void *p = nullptr;
+    if (hipHostMalloc(&p, cap) != hipSuccess) {
+        (void)hipGetLastError();
+        cap = bytes;
+        if (hipHostMalloc(&p, cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return FASTMDP_E_NOMEM;
+        }
+    }
     if (c->hGather) hipHostFree(c->hGather);
-    c->hGather = nullptr;
-    c->gather_cap = 0;
-    if (hipHostMalloc(&c->hGather, cap) != hipSuccess) return FASTMDP_E_NOMEM;
+    c->hGather = p;
     c->gather_cap = cap;
     return 0;
 }
 
+// No pinned buffer to be had: the trajectories copied one by one into the
+// caller's plans (the streams that wrote them have been waited for).
+int plans_copy(fastmdp_ctx *c, const std::vector<int> &slots, const std::vector<int> &reqs, const Slot *hs,
+               fastmdp_plan *plans) {
+    for (size_t i = 0; i < slots.size(); ++i) {
+        const Slot &s = hs[slots[i]];
+        fastmdp_plan &p = plans[reqs[i]];
+        const size_t base = (size_t)slots[i] * c->stride, n = (size_t)s.n_points;
+        HIP_TRY(hipMemcpy(p.xyz, c->tr.xyz + base * 3, n * 3 * sizeof(double), hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(p.action, c->tr.act + base, n * sizeof(int), hipMemcpyDeviceToHost));
+        HIP_TRY(hipMemcpy(p.value, c->tr.val + base, n * sizeof(double), hipMemcpyDeviceToHost));
+        p.status = s.status;
+        p.t0 = s.t0;
+        p.n_points = s.n_points;
+    }
+    return 0;
+}
+
+// pp: the trajectories that are on their way (none without memory for the
+// buffer: they are in the caller's plans on return).
+
 int gather_enqueue(fastmdp_ctx *c, const Slot *dslots, const std::vector<int> &slots, const std::vector<int> &reqs, const Slot *hs,
-                   const fastmdp_plan *plans, PendingPlans &pp) {
+                   fastmdp_plan *plans, PendingPlans &pp) {
     const int m = (int)slots.size();
     pp = PendingPlans();
-    pp.slots = slots;
-    pp.reqs = reqs;
-    pp.off.resize(m);
+    PendingPlans q;
+    q.slots = slots;
+    q.reqs = reqs;
+    q.off.resize(m);
     for (int i = 0; i < m; ++i) {
         const Slot &s = hs[slots[i]];
         if (plans[reqs[i]].capacity < s.n_points) return FASTMDP_E_CAPACITY;
-        pp.off[i] = pp.total;
-        pp.total += s.n_points;
-        pp.n.push_back(s.n_points);
-        pp.status.push_back(s.status);
-        pp.t0.push_back(s.t0);
+        q.off[i] = q.total;
+        q.total += s.n_points;
+        q.n.push_back(s.n_points);
+        q.status.push_back(s.status);
+        q.t0.push_back(s.t0);
     }
-    const int grown = gather_reserve(c, (size_t)pp.total * kPointBytes);
-    if (grown) return grown;
     if (m > c->max_slots) return FASTMDP_E_CAPACITY;
-    std::memcpy(c->hList2, pp.slots.data(), m * sizeof(int));
-    std::memcpy(c->hOff, pp.off.data(), m * sizeof(long long));
+    if (gather_reserve(c, (size_t)q.total * kPointBytes)) return plans_copy(c, slots, reqs, hs, plans);
+    std::memcpy(c->hList2, q.slots.data(), m * sizeof(int));
+    std::memcpy(c->hOff, q.off.data(), m * sizeof(long long));
     // on the gathers' own stream, so that the planning stream's next launch
     // does not wait for the copy; the caller has synchronised the planning
     // stream, and nothing it runs before these slots are reused writes them
-    HIP_TRY(fmdp::launch_gather_traj(dslots, c->hList2, m, c->hOff, pp.total, c->tr, c->hGather, c->gstream));
+    HIP_TRY(fmdp::launch_gather_traj(dslots, c->hList2, m, c->hOff, q.total, c->tr, c->hGather, c->gstream));
     HIP_TRY(hipEventRecord(c->eGather, c->gstream));
+    pp = std::move(q);
     return 0;
 }
 
@@ -428,26 +472,29 @@ void gather_unpack(fastmdp_ctx *c, PendingPlans &pp, fastmdp_plan *plans) {
 // or long ones (above kDirectBytes) are packed once their lengths are known.
 constexpr size_t kDirectBytes = (size_t)8 << 20;
 
-bool direct_out(const fastmdp_ctx *c, int n) { return (size_t)n * c->stride * kPointBytes <= kDirectBytes; }
+// Before the planner's launch (the buffer may have to grow): whether the
+// trajectories go that way.
+bool plans_reserve(fastmdp_ctx *c, int n) {
+    const size_t bytes = (size_t)n * c->stride * kPointBytes;
+    return bytes <= kDirectBytes && gather_reserve(c, bytes) == 0;
+}
 
-int plans_enqueue(fastmdp_ctx *c, const Slot *slots, int n) {
-    if (!direct_out(c, n)) return 0;
-    const long long total = (long long)n * c->stride;
-    const int rc = gather_reserve(c, (size_t)total * kPointBytes);
-    if (rc) return rc;
+int plans_enqueue(fastmdp_ctx *c, const Slot *slots, int n, bool direct) {
+    if (!direct) return 0;
     for (int i = 0; i < n; ++i) {
         c->hList2[i] = i;
         c->hOff[i] = (long long)i * c->stride;
     }
-    HIP_TRY(fmdp::launch_gather_traj(slots, c->hList2, n, c->hOff, total, c->tr, c->hGather, c->stream));
+    HIP_TRY(fmdp::launch_gather_traj(slots, c->hList2, n, c->hOff, (long long)n * c->stride, c->tr, c->hGather,
+                                     c->stream));
     return 0;
 }
 
 // After the synchronisation that follows plans_enqueue; hs: the slots as the
 // planner left them.
-int plans_collect(fastmdp_ctx *c, const Slot *slots, const Slot *hs, int n, fastmdp_plan *plans) {
+int plans_collect(fastmdp_ctx *c, const Slot *slots, const Slot *hs, int n, bool direct, fastmdp_plan *plans) {
     PendingPlans pp;
-    if (direct_out(c, n)) {
+    if (direct) {
         pp.total = (long long)n * c->stride;
         for (int i = 0; i < n; ++i) {
             pp.reqs.push_back(i);
@@ -741,8 +788,10 @@ int fastmdp_eval_step(fastmdp_ctx *ctx, const fastmdp_state *state, double *valu
     const int A = ctx->A;
     double *h = ctx->hIo;
     EvalOut ev{h, h + A, h + 2 * A, h + 3 * A, ctx->hInt};
+    Drain drain{ctx};
     int rc = timed_planner(ctx, 1, nullptr, 1, 0, 0, ev, ctx->hSlots);
     if (rc) return rc;
+    drain.done = true;
     if (values) std::memcpy(values, h, A * sizeof(double));
     if (goal_term) std::memcpy(goal_term, h + A, A * sizeof(double));
     if (intr_term) std::memcpy(intr_term, h + 2 * A, A * sizeof(double));
@@ -761,16 +810,19 @@ int fastmdp_plan_request(fastmdp_ctx *ctx, const fastmdp_request *req, fastmdp_p
     reset_stats(ctx);
     Slot &s = ctx->hSlots[0];                          // the kernel reads and writes it in place
     s = fresh_slot(*req, 0, ctx->seq);
+    const bool direct = plans_reserve(ctx, 1);
+    Drain drain{ctx};
     int rc = refresh_grid(ctx, ctx->seq, false);
     if (rc) return rc;
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
     rc = timed_planner(ctx, 1, nullptr, ctx->cfg.max_steps + 1, 0, 0, none, ctx->hSlots, 0, false);
-    rc = rc ? rc : plans_enqueue(ctx, ctx->hSlots, 1);
+    rc = rc ? rc : plans_enqueue(ctx, ctx->hSlots, 1, direct);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     rc = planner_time(ctx);
-    rc = rc ? rc : plans_collect(ctx, ctx->hSlots, ctx->hSlots, 1, out);
+    rc = rc ? rc : plans_collect(ctx, ctx->hSlots, ctx->hSlots, 1, direct, out);
     if (rc) return rc;
+    drain.done = true;
     ctx->st_pairs = s.pairs;
     ctx->st_entries = s.entries;
     ctx->st_steps = s.steps;
@@ -796,16 +848,19 @@ int fastmdp_plan_departures(fastmdp_ctx *ctx, const fastmdp_request *req, int32_
         r.t0 = t0[i];
         hs[i] = fresh_slot(r, i, ctx->seq);            // every candidate sees the same table
     }
+    const bool direct = plans_reserve(ctx, n);
+    Drain drain{ctx};
     int rc = refresh_grid(ctx, ctx->seq, false);
     if (rc) return rc;
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
     rc = timed_planner(ctx, n, nullptr, ctx->cfg.max_steps + 1, 1, 0, none, hs, 0, false);
-    rc = rc ? rc : plans_enqueue(ctx, hs, n);
+    rc = rc ? rc : plans_enqueue(ctx, hs, n, direct);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(ctx->stream));
     rc = planner_time(ctx);
-    rc = rc ? rc : plans_collect(ctx, hs, hs, n, plans);
+    rc = rc ? rc : plans_collect(ctx, hs, hs, n, direct, plans);
     if (rc) return rc;
+    drain.done = true;
     int best = -1;
     for (int i = 0; i < n; ++i) {
         ctx->st_pairs += hs[i].pairs;
@@ -831,6 +886,8 @@ int fastmdp_plan_batch(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs,
     reset_stats(ctx);
     Slot *hs = ctx->hSlots;
     for (int i = 0; i < n; ++i) hs[i] = fresh_slot(reqs[i], i, ctx->seq);
+    const bool direct = plans_reserve(ctx, n);
+    Drain drain{ctx};
     HIP_TRY(hipMemcpyAsync(ctx->dSlots, hs, n * sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     const fmdp::MatePeaks mates{ctx->bs.pk, ctx->bs.owner, ctx->bs.n};
     EvalOut none{nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -867,7 +924,7 @@ int fastmdp_plan_batch(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs,
         }
     }
     HIP_TRY(hipEventRecord(ctx->e1, ctx->stream));
-    rc = plans_enqueue(ctx, ctx->dSlots, n);
+    rc = plans_enqueue(ctx, ctx->dSlots, n, direct);
     if (rc) return rc;
     HIP_TRY(hipMemcpyAsync(hs, ctx->dSlots, n * sizeof(Slot), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
@@ -879,7 +936,9 @@ int fastmdp_plan_batch(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs,
         ctx->st_entries += hs[i].entries;
         ctx->st_steps += hs[i].steps;
     }
-    return plans_collect(ctx, ctx->dSlots, hs, n, plans);
+    rc = plans_collect(ctx, ctx->dSlots, hs, n, direct, plans);
+    drain.done = rc == 0;
+    return rc;
 }
 
 int fastmdp_commit_plan(fastmdp_ctx *ctx, const fastmdp_plan *plan) {
@@ -891,8 +950,10 @@ int fastmdp_commit_plan(fastmdp_ctx *ctx, const fastmdp_plan *plan) {
     for (int k = 0; k < n; ++k)
         if (ctx->hRowN[t0 + k] >= ctx->tb.cap) return FASTMDP_E_CAPACITY;
     std::memcpy(ctx->hPts, plan->xyz, (size_t)n * 3 * sizeof(double));
+    Drain drain{ctx};
     HIP_TRY(fmdp::launch_commit(ctx->dc, ctx->tb, ctx->hPts, t0, n, ctx->seq, ctx->dFlag, ctx->hInt + 1, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    drain.done = true;
     const int flag = ctx->hInt[1];
     if (flag & 2) return FASTMDP_E_CAPACITY;
     if (flag) return FASTMDP_E_CONFLICT;
@@ -1058,7 +1119,7 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
             if (!acc_slots.empty()) {
                 int rc = gather_enqueue(ctx, ctx->dSlots, acc_slots, acc_reqs, hs, plans, pending);
                 if (rc) return finish(rc);
-                gathered = true;
+                gathered = gathered || !pending.empty();
                 for (int s : acc_slots) slot_req[s] = -1;   // reusable: the gather precedes any new planning
             }
         }
@@ -1079,8 +1140,9 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
     // accepted are withdrawn.  Accepted trajectories still on their way to
     // the caller are delivered; committed[] is 0 from the first unaccepted
     // request on.
-    hipStreamSynchronize(ctx->stream);
-    if (!pending.empty() && hipEventSynchronize(ctx->eGather) == hipSuccess) gather_unpack(ctx, pending, plans);
+    (void)hipStreamSynchronize(ctx->stream);
+    const bool gathered_all = hipStreamSynchronize(ctx->gstream) == hipSuccess;
+    if (!pending.empty() && gathered_all) gather_unpack(ctx, pending, plans);
     int m = 0;
     for (int s = 0; s < S; ++s)
         if (slot_req[s] >= 0) ctx->hPass[m++] = s;
@@ -1180,6 +1242,7 @@ int fastmdp_eval_proposal(fastmdp_ctx *ctx, const fastmdp_state *state, float *f
     r.goal = state->goal;
     r.t0 = state->t;
     Slot s = fresh_slot(r, 0, ctx->seq);
+    Drain drain{ctx};
     HIP_TRY(hipMemcpyAsync(ctx->dSlots, &s, sizeof(Slot), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(hipMemsetAsync(ctx->dEvF, 0, (FASTMDP_N_FEAT + fmdp::kMaxActions) * sizeof(float), ctx->stream));
     const int A = ctx->A;
@@ -1192,6 +1255,7 @@ int fastmdp_eval_proposal(fastmdp_ctx *ctx, const fastmdp_state *state, float *f
     HIP_TRY(hipMemcpyAsync(hf.data(), ctx->dEvF, hf.size() * sizeof(float), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipMemcpyAsync(hi, ctx->dEvI, sizeof(hi), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(hipStreamSynchronize(ctx->stream));
+    drain.done = true;
     if (features) std::memcpy(features, hf.data(), FASTMDP_N_FEAT * sizeof(float));
     if (logits) std::memcpy(logits, hf.data() + FASTMDP_N_FEAT, A * sizeof(float));
     if (topk) std::memcpy(topk, hi, ctx->prop.k * sizeof(int));
