@@ -169,7 +169,11 @@ typedef struct {
 
 /* Create a context on the current HIP device: allocates the time-major
  * structure-of-arrays plan table (max_rows x plan_capacity FP32 x, y, z) and
- * per-slot trajectory buffers.  Errors: E_INVAL (unsupported action-set
+ * per-slot trajectory buffers.  With range_query = 1 and planner_threads 0,
+ * 256 or 512 also an index of the rows (20 bytes per table entry, beside the
+ * table's 24, and 4 KB per row); without memory for it the context is made
+ * all the same and plans on the 1024-thread kernel (the same plans, more
+ * slowly).  Errors: E_INVAL (unsupported action-set
  * shape or bad constant), E_NOMEM, E_DEVICE.  *out is set only on success. */
 int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out);
 

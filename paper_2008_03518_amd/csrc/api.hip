@@ -316,6 +316,23 @@ int timed_planner(fastmdp_ctx *c, int nblk, const int *list, int budget, int val
     return planner_time(c);
 }
 
+// The range-query planner's index of the rows, after everything a context
+// cannot do without.  Where there is no memory for it (20 bytes an entry and
+// 4 KB a row, beside the table's 24 bytes an entry) the requests are planned
+// on the 1024-thread kernel, which reads the table itself: the same plans.
+void alloc_index(fastmdp_ctx *c) {
+    DevTable &t = c->tb;
+    const size_t rows = (size_t)c->cfg.max_rows, entries = rows * c->cfg.plan_capacity;
+    if (dev_alloc(&t.Q, entries) == 0 && dev_alloc(&t.grec, entries) == 0 &&
+        dev_alloc(&t.goff, rows * (fmdp::kGridCells + 1)) == 0 && dev_alloc(&t.gn, rows) == 0)
+        return;
+    hipFree(t.Q); hipFree(t.grec); hipFree(t.goff); hipFree(t.gn);
+    t.Q = nullptr;
+    t.grec = nullptr;
+    t.goff = t.gn = nullptr;
+    c->dc.planner_threads = fmdp::kPlanThreads;
+}
+
 // The rows' grids, before a range-query planner launch: built when there are
 // none, or when the entries appended since (searched one by one) have grown
 // to a quarter of the indexed ones.  `limit` as launch_build_grid; in_call:
@@ -550,12 +567,6 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
     rc = rc ? rc : dev_alloc(&c->tb.vis, tsz);
     rc = rc ? rc : dev_alloc(&c->tb.own, tsz);
     rc = rc ? rc : dev_alloc(&c->tb.dead, tsz);
-    if (fmdp::uses_range_planner(c->dc, FASTMDP_PROPOSE_NONE)) {
-        rc = rc ? rc : dev_alloc(&c->tb.Q, tsz);
-        rc = rc ? rc : dev_alloc(&c->tb.grec, tsz);
-        rc = rc ? rc : dev_alloc(&c->tb.goff, (size_t)cfg->max_rows * (fmdp::kGridCells + 1));
-        rc = rc ? rc : dev_alloc(&c->tb.gn, (size_t)cfg->max_rows);
-    }
     rc = rc ? rc : dev_alloc(&c->tb.rowN, (size_t)cfg->max_rows);
     rc = rc ? rc : dev_alloc(&c->dSlots, (size_t)c->max_slots);
     rc = rc ? rc : dev_alloc(&c->tr.xyz, ssz * 3);
@@ -628,6 +639,7 @@ int fastmdp_create(const fastmdp_config *cfg, fastmdp_ctx **out) {
         delete c;
         return rc;
     }
+    if (fmdp::uses_range_planner(c->dc, FASTMDP_PROPOSE_NONE)) alloc_index(c);
     c->stream = c->own;
     c->tr.stride = c->stride;
     {

@@ -1,8 +1,8 @@
 """The host side of the library when memory or a launch fails, on a pretended
 device (tests/host/fake_api.hip, the CPU): a call that ends early leaves
 nothing in flight that reads or writes the context's pinned memory, plans
-arrive without the pinned buffer, and the next call is not told of an error
-that was dealt with."""
+arrive without the pinned buffer, the next call is not told of an error that
+was dealt with, and a context needs no memory for the range query's index."""
 import os
 import re
 import shutil
@@ -57,3 +57,11 @@ def test_a_launch_that_fails(fake, call, n):
     first, second = fake(call, n, "no_gather")
     assert first["rc"] == E_DEVICE and first["pending"] == 0
     assert second["rc"] == 0 and second["whole"] == 1 and second["pending"] == 0
+
+
+def test_without_memory_for_the_index(fake):
+    """The context is made, and plans on the kernel that reads the table
+    itself (one that needs the index would be refused by its launcher)."""
+    for call in fake("no_index", 1):
+        assert call["rc"] == 0 and call["whole"] == 1 and call["pending"] == 0
+        assert call["range"] == 0 and call["other"] > 0
