@@ -11,8 +11,11 @@ plans.  Timed legs, all committing identical plans:
     sweeps only the plans within reach of the state, Sec. VII) on the
     range-query planner (256-thread workgroups, four requests per compute
     unit, or 512-thread workgroups, one per compute unit, for a launch that
-    holds no more requests than compute units), with a memory-side roofline (row bytes streamed); beside it the
-    same on the 1024-thread kernel (one request per compute unit);
+    holds no more requests than compute units): a chain of dependent
+    operations a step, reported as steps per microsecond beside what the
+    counters say it draws from HBM; beside it the same on the 1024-thread
+    kernel (one request per compute unit), with a memory-side roofline (row
+    bytes streamed);
   * the plain full sweep (every plan, every action), with its roofline
     against the FP32 vector peak;
   * the learned action proposal (trained beforehand, untimed, with the
@@ -45,20 +48,20 @@ FP64_VECTOR_PEAK_TFLOPS = 78.6      # MI355X published FP64 vector peak
 HBM_PEAK_GBPS = 8000.0              # MI355X published HBM3E bandwidth
 FLOPS_PER_PAIR = 8                  # 3 sub + 3 mul + 2 add for one squared distance
 ROW_ENTRY_BYTES = 16                # one table row entry read by a 1024-thread step: x, y, z, visibility
-RANGE_ENTRY_BYTES = 8               # one row entry read by the range-query planner's box test: x, y
 
 # HBM bytes per planner launch on this workload, from the FETCH_SIZE /
 # WRITE_SIZE counter runs in profiles/planner_traffic__*.md (calibrated on a
 # copy of known size), valid only for the kernel sources they were taken on.
-TRAFFIC_SOURCES = ("planner.hip", "range.hip", "planner.h", "score.h", "proposal.h", "wave.h")
-TRAFFIC_SHA256 = "23f389133fa73a82ee227b98009cf74962fa19b1ade96c32f7a36e31e60fd4cc"
+TRAFFIC_SOURCES = ("planner.hip", "range.hip", "planner.h", "score.h", "proposal.h", "wave.h", "bearing.h",
+                   "row_window.h")
+TRAFFIC_SHA256 = "921d1f86f1399cbda45e5b239e5d30aa24802077267c8668f6b9dcf2d38d7bc3"
 # VALU counters per planner launch of an FCFS pass (profiles/planner_valu__*.md),
 # valid for the same sources: the share of SIMD cycles issuing VALU work and
 # the FLOP the hardware counts (FP32 for the sweep, FP64 for the range-query
-# planner's valuation), beside the algorithmic rooflines
-VALU_COUNTERS = {"full_sweep": {"valu_busy": 0.582, "hw_fp32_flops_per_launch": 4.64e10},
-                 "range_query": {"valu_busy": 0.169, "hw_fp64_flops_per_launch": 2.1e09}}
-TRAFFIC_BYTES_PER_LAUNCH = {"range_query": 5.03e08, "range_query_1024": 3.81e08, "proposal": 7.2e08, "full_sweep": 3.57e08}
+# planner), beside the algorithmic rooflines
+VALU_COUNTERS = {"full_sweep": {"valu_busy": 0.608, "hw_fp32_flops_per_launch": 5.71e10},
+                 "range_query": {"valu_busy": 0.088, "hw_fp64_flops_per_launch": 4.4e08}}
+TRAFFIC_BYTES_PER_LAUNCH = {"range_query": 4.54e07, "range_query_1024": 4.34e08, "proposal": 8.1e08, "full_sweep": 6.83e08}
 
 
 def _sources_match() -> bool:
@@ -185,12 +188,12 @@ def _roofline(r, leg):
     }
 
 
-def _roofline_rows(r, leg, entry_bytes=RANGE_ENTRY_BYTES):
-    """Memory-side roofline of a leg that sweeps few pairs: the table rows it
-    streams per planner-kernel second (entry_bytes per row entry per step:
-    x and y for the range-query planner's box test, x, y, z and visibility
-    for the 1024-thread kernel), against the HBM peak."""
-    achieved = entry_bytes * r["entries"] / (r["kms"] * 1e-3) / 1e9
+def _roofline_rows(r, leg):
+    """Memory-side roofline of the 1024-thread kernel with the range query,
+    which sweeps few pairs: the table rows it streams per planner-kernel
+    second (x, y, z and visibility of every entry of a step's row), against
+    the HBM peak."""
+    achieved = ROW_ENTRY_BYTES * r["entries"] / (r["kms"] * 1e-3) / 1e9
     return {
         "bound": "hbm",
         "achieved": achieved,
@@ -201,8 +204,32 @@ def _roofline_rows(r, leg, entry_bytes=RANGE_ENTRY_BYTES):
         "traffic_unit": "HBM bytes per launch",
         "kernel": "planner_kernel",
         "avg_launch_ms": r["kms"] / max(r["launches"], 1),
-        "bytes_per_launch": entry_bytes * r["entries"] / max(r["launches"], 1),
+        "bytes_per_launch": ROW_ENTRY_BYTES * r["entries"] / max(r["launches"], 1),
         "counters": _counters(leg, r["kms"] / max(r["launches"], 1)),
+    }
+
+
+def _latency(r, leg):
+    """The range-query planner: its steps are chains of dependent operations
+    that look up a few records of a row's index, so neither the rows' bytes
+    nor the pairs are its work.  Steps per planner-kernel microsecond, and
+    against the HBM peak what the counters saw it fetch and write (None once
+    the sources differ from those they were taken on)."""
+    avg_ms = r["kms"] / max(r["launches"], 1)
+    traffic = _traffic(leg)
+    achieved = None if traffic is None else traffic / (avg_ms * 1e-3) / 1e9
+    return {
+        "bound": "latency",
+        "steps_per_us": r["steps"] / (r["kms"] * 1e3),
+        "achieved": achieved,
+        "peak": HBM_PEAK_GBPS,
+        "unit": "GB/s",
+        "frac": None if achieved is None else achieved / HBM_PEAK_GBPS,
+        "traffic": traffic,
+        "traffic_unit": "HBM bytes per launch",
+        "kernel": "range_planner_kernel",
+        "avg_launch_ms": avg_ms,
+        "counters": _counters(leg, avg_ms),
     }
 
 
@@ -424,7 +451,7 @@ def main():
         "status_counts": {S.STATUS_NAMES[int(k)]: int((status == k).sum()) for k in np.unique(status)},
         "pairs_swept_per_step": rq["pairs"] / len(rq["times"]),
         "pairs_of_full_sweep_per_step": full["pairs"] / len(full["times"]),
-        "roofline": _roofline_rows(rq, "range_query"),
+        "roofline": _latency(rq, "range_query"),
         "full_sweep": {
             "value": full["value"], "ms_per_step": full["ms_per_step"], "planner_steps": full["steps"],
             "pair_evals_per_s": full["pairs"] / (full["kms"] * 1e-3), "resumes": full["resumes"],
@@ -456,7 +483,7 @@ def main():
         "resumes": rq1["resumes"],
         "identical_to_full_sweep": bool(_same_plans(rq1["plans"], full["plans"])
                                         and np.array_equal(rq1["committed"], full["committed"])),
-        "roofline": _roofline_rows(rq1, "range_query_1024", ROW_ENTRY_BYTES)}
+        "roofline": _roofline_rows(rq1, "range_query_1024")}
     # the planners alone, without the FCFS order: one launch planning request
     # 3 from 1024 departure rows at once (every CU busy), planner steps per us
     out["kernel_steady_state"] = {}

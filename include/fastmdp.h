@@ -313,9 +313,11 @@ int fastmdp_table_rewind(fastmdp_ctx *ctx);
  * _plan_departures, _plan_batch, _eval_step): pair evaluations (action x
  * plan swept per step), steps taken, resumes, planner launches, summed
  * planner-kernel time in milliseconds measured with HIP events on the
- * context's stream, and table row entries read (each step reads the
- * successor's row, 16 bytes per entry: x, y, z, visibility; every window
- * row with a window).  Any pointer may be NULL. */
+ * context's stream, and entries of the table rows scored (the successor's
+ * row at each step; every window row with a window).  The 1024-thread kernel
+ * and the proposal path read 16 bytes of each (x, y, z, visibility); the
+ * range query on 256 or 512 threads looks a few up in an index of the row,
+ * so the count is no measure of its bytes.  Any pointer may be NULL. */
 int fastmdp_last_stats(const fastmdp_ctx *ctx, int64_t *pairs, int64_t *steps, int64_t *resumes,
                        int64_t *launches, double *kernel_ms, int64_t *row_entries);
 

@@ -301,10 +301,9 @@ int planner_time(fastmdp_ctx *c) {
 
 int timed_planner(fastmdp_ctx *c, int nblk, const int *list, int budget, int validate, int epoch,
                   const EvalOut &ev, Slot *slots, int stop_target = 0, bool sync = true) {
-    const int nt = fmdp::kPlanThreads;
     HIP_TRY(hipEventRecord(c->e0, c->stream));
     const fmdp::LaunchStop stop{c->dStop, stop_target};
-    hipError_t e = fmdp::launch_planner(nblk, nt, c->stream, c->dc, c->tb, slots, list, c->tr, budget, validate,
+    hipError_t e = fmdp::launch_planner(nblk, c->stream, c->dc, c->tb, slots, list, c->tr, budget, validate,
                                         epoch, ev, c->prop, stop, fmdp::MatePeaks{});
     if (e != hipSuccess) {
         std::fprintf(stderr, "libfastmdp: planner launch failed: %s\n", hipGetErrorString(e));
@@ -908,7 +907,7 @@ int fastmdp_plan_batch(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs,
     // the origin checks (no step), then each step: one planner step of every
     // aircraft still flying, then the batch's own rules and the next peaks
     auto planner = [&](int budget) -> int {
-        hipError_t e = fmdp::launch_planner(n, fmdp::kPlanThreads, ctx->stream, ctx->dc, ctx->tb, ctx->dSlots, nullptr,
+        hipError_t e = fmdp::launch_planner(n, ctx->stream, ctx->dc, ctx->tb, ctx->dSlots, nullptr,
                                             ctx->tr, budget, 0, 0, none, ctx->prop, nostop,
                                             budget > 0 ? mates : fmdp::MatePeaks{});
         if (e != hipSuccess) {
@@ -1040,8 +1039,10 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
             // proposal or the window one: their workgroups take a CU each; the
             // range-query planner could hold four, but the oldest requests,
             // which the later ones depend on, then step more slowly; the full
-            // sweep: 78 ms a pass of 1000 requests at 3000 plans with two, 88
-            // with one), for up to `budget` steps: a
+            // sweep, ms a pass with two and with one: 1000 requests at 3000
+            // plans 77 and 75, 92 and 85, 78 and 84 by the inputs, at 1500
+            // plans 57 and 65, 2000 requests at 800 plans 91 and 108), for up
+            // to `budget` steps: a
             // request that waits for the next launch plans against the plans its
             // predecessors finish in this one instead of re-planning after them
             list.clear();
@@ -1076,10 +1077,11 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
                 // the others resume after the acceptance pass, with new requests
                 // in the freed compute units.  In the range-query planner's
                 // launches few requests wait for a place after the first ones, so
-                // they run until half have finished (fewer acceptance passes;
-                // measured: about 10 % shorter FCFS passes than with a quarter;
-                // the full sweep, whose steps cost more than a pass, takes 79 ms
-                // with a quarter and 91 with half)
+                // they run until half have finished (half the acceptance passes;
+                // three streams of 1000 requests: 9.4, 10.2 and 10.0 ms a pass,
+                // with a quarter 9.7, 10.1 and 11.3; the full sweep, whose steps
+                // cost more than a pass, takes 76, 91 and 77 ms with a quarter
+                // and 92, 102 and 90 with half)
                 const int stop_div = fmdp::uses_range_planner(ctx->dc, ctx->prop.mode) ? 2 : 4;
                 const int stop_target = std::max(1, (int)list.size() / stop_div);
                 int rc = timed_planner(ctx, (int)list.size(), ctx->hList, budget, 1, epoch, none, ctx->dSlots, stop_target, false);

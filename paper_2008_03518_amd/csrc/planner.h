@@ -263,9 +263,10 @@ struct BatchState {
     int *any;        // 1 while an aircraft is flying (pinned host memory)
 };
 
-// nt: workgroup size; kPlanThreads is the one built.  prop.mode selects the
-// proposal path (FASTMDP_PROPOSE_NONE: full sweep only).
-hipError_t launch_planner(int nblk, int nt, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
+// prop.mode selects the proposal path (FASTMDP_PROPOSE_NONE: full sweep
+// only); the configuration, the launch's size and the outputs asked for select
+// the kernel and its workgroup.
+hipError_t launch_planner(int nblk, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
                           const int *list, const Traj &tr, int budget, int validate, int epoch, const EvalOut &ev,
                           const PropArgs &prop, const LaunchStop &stop, const MatePeaks &mates = MatePeaks{});
 

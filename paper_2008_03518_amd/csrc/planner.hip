@@ -1212,9 +1212,10 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
             // within the tie band's distance, it is the argmax, and its value
             // is its goal term, which is computed while the next step runs.
             // Ties, distances within kBand of the radius and terrain wells go to
-            // the scoring below.  Five requests planned in turn at 50 plans and
-            // 81 actions: 5.8 ms with every action scored, 4.2 ms (with the
-            // slices above).
+            // the scoring below.  Eight requests planned in turn, ms, with every
+            // action scored and this way: 50 plans and 81 actions 6.0 and 5.3,
+            // 2000 plans and 360 actions 73.7 and 70.1; over terrain, where most
+            // steps lie in its well, 29.8 and 30.4.
             if constexpr (QUICK) {
                 const double far = br + fabs(g[2] - s[2]);
                 if (cfg.detour_ok && br > 1e-50 && far <= cfg.run_dmax) {      // uniform
@@ -1430,10 +1431,9 @@ __global__ __launch_bounds__(NT, (PlanGeom<NT, PROP>::OCC)) void planner_kernel(
 // launch dispatch over the supported (climbs, speeds, zero-climb) shapes
 // ---------------------------------------------------------------------------
 template <int NC, int NV, int ZC>
-static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
+static hipError_t launch_t(int nblk, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
                            const int *list, const Traj &tr, int budget, int validate, int epoch, const EvalOut &ev,
                            const PropArgs &prop, const LaunchStop &stop, const MatePeaks &mates) {
-    (void)nt;
     if (c.lookahead > 1 && c.range_query)
         hipLaunchKernelGGL((planner_kernel<kPlanThreads, NC, NV, ZC, false, true, true>), dim3(nblk),
                            dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
@@ -1451,8 +1451,9 @@ static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, co
                            dim3(kPlanThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (uses_pairs(c, prop.mode) && nblk > c.n_cu)
         // two requests per CU: one sweeps while the other stages its row and
-        // chooses (of a 16 us step at 2700 plans and 360 actions the sweep is
-        // 10.7); no more requests than CUs step faster on 16 waves each
+        // chooses (one launch of 1000 departures at 3000 plans and 360
+        // actions: 31 ms, one per CU on 16 waves 42); no more requests than
+        // CUs step faster on 16 waves each
         hipLaunchKernelGGL((planner_kernel<kPairThreads, NC, NV, ZC, false, false, false, true>), dim3(nblk),
                            dim3(kPairThreads), 0, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
     else if (prop.mode == FASTMDP_PROPOSE_NONE)
@@ -1469,9 +1470,9 @@ static hipError_t launch_t(int nblk, int nt, hipStream_t st, const DevCfg &c, co
 
 #define FMDP_SHAPE(NC, NV, ZC) \
     if (c.n_climb == NC && c.n_speed == NV && zc == ZC) \
-        return launch_t<NC, NV, ZC>(nblk, nt, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
+        return launch_t<NC, NV, ZC>(nblk, st, c, t, s, list, tr, budget, validate, epoch, ev, prop, stop, mates);
 
-hipError_t launch_planner(int nblk, int nt, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
+hipError_t launch_planner(int nblk, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s,
                           const int *list, const Traj &tr, int budget, int validate, int epoch, const EvalOut &ev,
                           const PropArgs &prop, const LaunchStop &stop, const MatePeaks &mates) {
     const int zc = c.zero_climb;

@@ -12,8 +12,8 @@
 //   - in a run, where no plan changes the choice: an action's value is at
 //     most its goal term, so the goal-directed action is the choice while no
 //     well reaches its successor.  One wave computes the run's states ahead
-//     (280 cycles a step: a reciprocal square root and its refinement), the
-//     others check them against the table;
+//     (about 300 cycles a step: a reciprocal square root and its
+//     refinements), the others check them against the table;
 //   - in a detour batch, among the plans near them: the action nearest the
 //     goal outside every well, one workgroup barrier a step and no
 //     exponential;
@@ -27,8 +27,9 @@
 // unit's 64 B/clk); columns appended since the grid was built are searched by
 // their 16-bit coordinates, 4 bytes an entry.  Points are written 64 at a
 // time, a run's values evaluated 64 at a time.
-//   Measured (MI355X, 3000 plans, 360 actions): a request alone 3.5 -> 0.30 us
-// a step; the 1000-request stream's planner time 22.3 -> 9.6 ms.
+//   Measured (MI355X, 3000 plans, 360 actions): a request alone 3.5 us a step
+// before, now 0.2 (no plan near) to 3 (in traffic all the way), 0.4 in the
+// middle of 180 flights; the 1000-request stream's planner time 22.3 -> 7.4 ms.
 #include "bearing.h"
 #include "planner.h"
 #include "row_window.h"
@@ -77,7 +78,7 @@ __global__ __attribute__((amdgpu_flat_work_group_size(NT, NT),
     __shared__ double sR[2][NW][5];
     __shared__ int sRa[2][NW], sRn[2][NW];
     __shared__ double sC0[HMAX], sS0[HMAX];              // heading offsets (cos, sin of 2*pi*h/H)
-    __shared__ float4 tile[TILE];               // staged entries of one round; validation point list
+    __shared__ float4 tile[TILE];               // staged entries of one round
     __shared__ double sCos[2][HMAX], sSin[2][HMAX];      // heading directions, alternate steps
     __shared__ double sStep[FASTMDP_MAX_ACT_DIM], sDz[FASTMDP_MAX_ACT_DIM];   // speed*dt, climb*dt
     __shared__ float sKv[FASTMDP_MAX_ACT_DIM], sClf[FASTMDP_MAX_ACT_DIM];      // FP32 sweep constants

@@ -703,9 +703,8 @@ __global__ __launch_bounds__(kPassThreads) void fcfs_abort_kernel(DevTable tb, S
     }
 }
 
-// Pack the trajectories of the listed slots into one buffer for a single
-// device-to-host copy: slot list[i]'s n_points points go to point offset
-// off[i]; xyz (3 doubles), then action, then value per point, in three
+// Pack the trajectories of the listed slots into one pinned host buffer: slot
+// list[i]'s n_points points go to point offset off[i]; xyz (3 doubles), then action, then value per point, in three
 // contiguous sections of `total` points each.
 // Consecutive threads write consecutive words (dst may lie across the bus).
 __global__ void gather_traj_kernel(const Slot *slots, const int *list, const long long *off, long long total, Traj tr,

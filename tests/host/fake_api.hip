@@ -158,7 +158,7 @@ size_t features_workspace(int) { return 1; }
 int mlp_weights(const fastmdp_mlp *, PropNet *) { return -1; }
 
 // Every running request reaches its goal in 600 + id % 3 points of its own.
-hipError_t launch_planner(int nblk, int, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s, const int *list,
+hipError_t launch_planner(int nblk, hipStream_t st, const DevCfg &c, const DevTable &t, Slot *s, const int *list,
                           const Traj &tr, int budget, int, int, const EvalOut &ev, const PropArgs &prop,
                           const LaunchStop &, const MatePeaks &) {
     const bool range = uses_range_planner(c, prop.mode) && !ev.V && budget > 1;
