@@ -101,9 +101,10 @@ typedef struct {
                                         per compute unit and 256 for a larger
                                         one, else 1024 (a full sweep's launch
                                         of more requests than compute units: 512,
-                                        two per compute unit); the proposal path
-                                        keeps
-                                        its own workgroup and single-step
+                                        two per compute unit, while the longest
+                                        row holds at most 4096 entries, 2048
+                                        with more than 64 headings); the proposal
+                                        path keeps its own workgroup and single-step
                                         outputs and co-simulated batches the
                                         1024-thread one.  Every choice gives
                                         the same plans bit for bit               */

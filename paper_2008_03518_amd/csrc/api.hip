@@ -347,6 +347,9 @@ int refresh_grid(fastmdp_ctx *c, int limit, bool in_call) {
     return 0;
 }
 
+// The table's rows, for the choice of the kernel of launches of many requests.
+void note_rows(fastmdp_ctx *c) { c->dc.longest_row = *std::max_element(c->hRowN.begin(), c->hRowN.end()); }
+
 void reset_stats(fastmdp_ctx *c) {
     c->st_pairs = c->st_steps = c->st_resumes = c->st_launches = c->st_entries = 0;
     c->st_hit = c->st_miss = 0;
@@ -853,6 +856,7 @@ int fastmdp_plan_departures(fastmdp_ctx *ctx, const fastmdp_request *req, int32_
     }
     std::lock_guard<std::mutex> lk(ctx->mu);
     reset_stats(ctx);
+    note_rows(ctx);
     Slot *hs = ctx->hSlots;
     for (int i = 0; i < n; ++i) {
         fastmdp_request r = *req;
@@ -987,6 +991,7 @@ int fastmdp_plan_fcfs(fastmdp_ctx *ctx, int32_t n, const fastmdp_request *reqs, 
     }
     std::lock_guard<std::mutex> lk(ctx->mu);
     reset_stats(ctx);
+    note_rows(ctx);
     using clk = std::chrono::steady_clock;
     const auto t_start = clk::now();
     auto now_s = [&]() { return std::chrono::duration<double>(clk::now() - t_start).count(); };

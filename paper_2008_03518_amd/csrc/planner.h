@@ -11,6 +11,8 @@ namespace fmdp {
 
 constexpr int kPlanThreads = 1024;  // planning workgroup: one request per CU, 16 wave64
 constexpr int kPairThreads = 512;   // full sweep of more requests than CUs: two per CU, 8 wave64 each
+constexpr int kPairTile = 2048;     // row entries they stage at a time (two workgroups share a CU's LDS)
+constexpr int kPairHeads = 64;      // headings up to which a pair's workgroup has eight slices
 constexpr int kPropThreads = 512;   // with the proposal path: 8 wave64, twice the registers per lane
 constexpr int kRangeThreads = 256;  // range-query planner: 4 wave64, up to four requests per CU
 constexpr int kRangePerCU = 4;      // range-query workgroups resident per CU (LDS and registers)
@@ -70,6 +72,7 @@ struct DevCfg {
     int detour_ok;                       // an action inside a well never beats one outside every well
     double clear_terr;                   // terrain clearance of a step that the goal term decides: clear of
                                          // the terrain well, and not below the surface (max(R_terr, 0))
+    int longest_row;                     // entries of the longest row when the call began (uses_pairs)
     int planner_threads;                 // full-sweep path: 0 (automatic), kRangeThreads, kRangeThreadsSolo,
                                          // kPlanThreads
     int n_cu;                            // compute units of the device
@@ -300,9 +303,17 @@ inline bool uses_range_planner(const DevCfg &c, int prop_mode) {
            c.planner_threads != kPlanThreads;
 }
 // A launch of the full sweep of more requests than CUs takes two per CU
-// (kPairThreads) unless the configuration asks for kPlanThreads.
+// (kPairThreads) unless the configuration asks for kPlanThreads, the longest
+// row has more entries than that kernel holds at once, or the headings leave
+// few slices a workgroup and the row is longer than a pair's tile.  Two
+// requests that share a CU step 1.3 (1000 plans) to 1.6 times (3000) as
+// slowly as alone, and past these limits up to 1.9 times, which a launch that
+// waits for one long flight then takes: 400 departures, ms with pairs and
+// without: 3000 plans, 81 actions 10.2 and 16.0; 5000 plans, 128 headings
+// 55.7 and 41.9; 9000 plans, 360 actions 51.7 and 48.1.
 inline bool uses_pairs(const DevCfg &c, int prop_mode) {
-    return !c.range_query && c.lookahead <= 1 && prop_mode == FASTMDP_PROPOSE_NONE && c.planner_threads != kPlanThreads;
+    return !c.range_query && c.lookahead <= 1 && prop_mode == FASTMDP_PROPOSE_NONE &&
+           c.planner_threads != kPlanThreads && c.longest_row <= (c.n_head <= kPairHeads ? 2 : 1) * kPairTile;
 }
 // The range-query planner's workgroup size for a launch of nblk requests: as configured, else
 // one request per CU on kRangeThreadsSolo threads when the launch holds no

@@ -61,8 +61,7 @@ constexpr int kMaxBackoff = 16;
 template <int NT, bool PROP>
 struct PlanGeom {
     static constexpr int NW = NT / 64;
-    // row entries per chunk (LDS tile): two workgroups of a pair share a CU's LDS
-    static constexpr int TILE = NT == kPairThreads && !PROP ? 2048 : 4096;
+    static constexpr int TILE = NT == kPairThreads && !PROP ? kPairTile : 4096;   // row entries per chunk (LDS tile)
     static constexpr int OCC = NT == kPropThreads && PROP ? 2 : 4;   // waves per SIMD (registers: 256 or 128)
     static constexpr int PRE = TILE / NT;                    // chunk entries per thread
     static constexpr int PRE4 = TILE / (4 * NT);             // 16-byte (four-entry) groups per thread
