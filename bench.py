@@ -54,14 +54,14 @@ ROW_ENTRY_BYTES = 16                # one table row entry read by a 1024-thread 
 # copy of known size), valid only for the kernel sources they were taken on.
 TRAFFIC_SOURCES = ("planner.hip", "range.hip", "planner.h", "score.h", "proposal.h", "wave.h", "bearing.h",
                    "row_window.h")
-TRAFFIC_SHA256 = "921d1f86f1399cbda45e5b239e5d30aa24802077267c8668f6b9dcf2d38d7bc3"
+TRAFFIC_SHA256 = "179e104c1b0548e9b177483774cf7e6b04f054c7c03a2a7dbf85051c70524bc7"
 # VALU counters per planner launch of an FCFS pass (profiles/planner_valu__*.md),
 # valid for the same sources: the share of SIMD cycles issuing VALU work and
 # the FLOP the hardware counts (FP32 for the sweep, FP64 for the range-query
 # planner), beside the algorithmic rooflines
-VALU_COUNTERS = {"full_sweep": {"valu_busy": 0.608, "hw_fp32_flops_per_launch": 5.71e10},
-                 "range_query": {"valu_busy": 0.088, "hw_fp64_flops_per_launch": 4.4e08}}
-TRAFFIC_BYTES_PER_LAUNCH = {"range_query": 4.54e07, "range_query_1024": 4.34e08, "proposal": 8.1e08, "full_sweep": 6.83e08}
+VALU_COUNTERS = {"full_sweep": {"valu_busy": 0.607, "hw_fp32_flops_per_launch": 5.90e10},
+                 "range_query": {"valu_busy": 0.089, "hw_fp64_flops_per_launch": 3.9e08}}
+TRAFFIC_BYTES_PER_LAUNCH = {"range_query": 4.79e07, "range_query_1024": 4.14e08, "proposal": 7.85e08, "full_sweep": 7.0e08}
 
 
 def _sources_match() -> bool:
