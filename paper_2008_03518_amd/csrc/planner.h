@@ -341,7 +341,8 @@ int mlp_weights(const fastmdp_mlp *m, PropNet *w);
 
 // table.hip
 hipError_t launch_fill_int(int *p, int value, int n, hipStream_t st);
-// The 16-bit coordinates of every entry in use (after a table was loaded whole).
+// The 16-bit coordinates of every place of the table (after points were read
+// from a file).
 hipError_t launch_quantise_table(const DevTable &t, hipStream_t st);
 // Every row's grid over its longest prefix of entries that stay as they are:
 // owned by sequence numbers below `limit` (accepted) or withdrawn.

@@ -47,10 +47,11 @@ __global__ void scatter_points_kernel(DevTable tb, const float *pts, const int *
     tb.dead[idx] = kAlive;
 }
 
-// One workgroup per row.
+// One workgroup per row, its whole capacity: a file that breaks off has
+// replaced points past the row's count too.
 __global__ void quantise_table_kernel(DevTable tb) {
-    const int row = blockIdx.x, n = min(tb.rowN[row], tb.cap);
-    for (int j = threadIdx.x; j < n; j += blockDim.x) {
+    const int row = blockIdx.x;
+    for (int j = threadIdx.x; j < tb.cap; j += blockDim.x) {
         const size_t idx = (size_t)row * tb.cap + j;
         tb.Q[idx] = quantised(tb, tb.X[idx], tb.Y[idx]);
     }

@@ -44,3 +44,39 @@ def test_plans_after_a_table_read_breaks_off(tmp_path, n_plans):
             assert a.status == b.status and a.n_points == b.n_points, q
             assert np.array_equal(a.points(), b.points()) and np.array_equal(a.actions(), b.actions()), q
             assert np.array_equal(a.values(), b.values()), q
+
+
+def test_points_past_the_row_count_follow_too(tmp_path):
+    """A file that breaks off replaces points past the counts of a table that
+    holds fewer; a rewind to a snapshot with more brings those back."""
+    from paper_2008_03518_amd import fastmdp as fm
+    sc = S.large_actions(seed=53, n_plans=60, n_requests=1)
+    sc.cfg.range_query = 1
+    other = S.make_known_plans(np.random.default_rng(54), sc.cfg, 60)
+    path, empty = str(tmp_path / "other"), str(tmp_path / "empty")
+    with fm.Context(sc.cfg) as ctx:
+        ctx.save_table(empty)
+        ctx.load_plans(other)
+        ctx.save_table(path)
+    with open(path, "r+b") as f:
+        f.truncate(f.seek(0, 2) * 3 // 4)
+    off = other.offsets()
+    fl = []
+    for j in range(12):                                  # head-on against the file's plans
+        a = other.xyz[off[j]:off[j + 1]].astype(float)
+        fl.append((a[min(200, len(a) - 1)], a[0], int(other.t0[j])))
+    got = []
+    for th in (1024, 0, 256):
+        with fm.Context(sc.cfg, planner_threads=th) as ctx:
+            ctx.load_plans(sc.plans)
+            ctx.snapshot()
+            ctx.load_table(empty)
+            with pytest.raises(fm.FastMDPError):
+                ctx.load_table(path)
+            ctx.rewind()
+            got.append([ctx.plan_request(*f) for f in fl])
+    print([(p.status, p.n_points) for p in got[0]], flush=True)
+    for plans in got[1:]:
+        for q, (a, b) in enumerate(zip(got[0], plans)):
+            assert a.status == b.status and a.n_points == b.n_points, q
+            assert np.array_equal(a.points(), b.points()) and np.array_equal(a.values(), b.values()), q
