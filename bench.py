@@ -54,7 +54,7 @@ ROW_ENTRY_BYTES = 16                # one table row entry read by a 1024-thread 
 # copy of known size), valid only for the kernel sources they were taken on.
 TRAFFIC_SOURCES = ("planner.hip", "range.hip", "planner.h", "score.h", "proposal.h", "wave.h", "bearing.h",
                    "row_window.h")
-TRAFFIC_SHA256 = "565d4b946659399922447cb1ec5795b0f4eed4604567a07316c9911135e92afe"
+TRAFFIC_SHA256 = "ef07dab709419c385ca53fe56b4181d9259b75367162aea18607674771796943"
 # VALU counters per planner launch of an FCFS pass (profiles/planner_valu__*.md),
 # valid for the same sources: the share of SIMD cycles issuing VALU work and
 # the FLOP the hardware counts (FP32 for the sweep, FP64 for the range-query

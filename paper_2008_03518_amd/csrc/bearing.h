@@ -2,9 +2,9 @@
 // from one approximate reciprocal square root (internal; plain arithmetic,
 // also compiled for the host).
 //
-// A square root and two divisions, each with its own seed, scaling and
-// iterations, take three times as long as this one chain, which the states of
-// a run follow one behind the other.  The results are rounded as theirs are:
+// The states of a run follow one behind the other, each behind a square root
+// and two divisions; one chain from one seed, without their scaling, is
+// shorter than the three.  The results are rounded as theirs are:
 // Goldschmidt's iteration and two exact remainders give the square root; the
 // reciprocal of the rounded distance, refined once more against it, is the
 // correctly rounded one (but for a chance of about 2^-37), and with such a
